@@ -48,6 +48,7 @@
 #include <type_traits>
 #include <thread>
 #include <unordered_map>
+#include <utility>
 #include <vector>
 
 #include "sdnn.h"
@@ -252,13 +253,25 @@ __global__ __launch_bounds__(256) void k_spread_to_masks(unsigned *__restrict__ 
 
 // With notify set, thread 0 finally stores (tag << 40) | (flags << 32) | count into that word of
 // coherent host memory, flags = bit 0: misc[0] (a layer-0 input is not 0 or 1), bit 1:
-// misc[kOverflowSlot] (the value dictionary is full); the host waits on it instead of a copy and a
-// stream synchronization.
+// misc[kOverflowSlot] (the value dictionary is full), bit 2: the sample below took more than
+// kDictSlots distinct values; the host waits on it instead of a copy and a stream synchronization.
+// With at least sample_min live rows, 4096 values of the layer's output are looked at: of feature-major
+// tiles (or, with sample_rows, rows by list position) act, whose segments with a clear seglive bit
+// are zero. A layer whose sample holds more values than the dictionary cannot be encoded, and the
+// attempt is saved (failed encodings took 0.7-1.2 ms on 16384 x 16384 activations whose values are many,
+// longer than a successful one, against 3-5 us for the sample).
+constexpr int kSampleValues = 4096;
+struct CompactSample {
+  const float *act;         // null: no sample
+  const unsigned *seglive;  // null: every segment is stored
+  int N, rows_major, min_rows;
+};
 __global__ __launch_bounds__(1024) void k_compact(unsigned *__restrict__ masks, int B, const int *__restrict__ ids_in,
                                                   int *__restrict__ ids_out, int *__restrict__ src_out,
                                                   const int *__restrict__ count_in, int *__restrict__ count_out,
                                                   int *__restrict__ count_out2, const int *__restrict__ misc,
-                                                  unsigned long long *__restrict__ notify, unsigned long long tag) {
+                                                  unsigned long long *__restrict__ notify, unsigned long long tag,
+                                                  CompactSample smp) {
   __shared__ int toff[kCompactTiles];
   __shared__ unsigned tmask[kCompactTiles];
   __shared__ int wsum[16];
@@ -311,11 +324,43 @@ __global__ __launch_bounds__(1024) void k_compact(unsigned *__restrict__ masks, 
     base += total;
     __syncthreads();
   }
+  // distinct values of the sample: an LDS hash table in place of the tile offsets; at most kDictSlots +
+  // 1024 of its slots fill up before every thread sees the count and stops
+  __shared__ int distinct;
+  static_assert(kDictSlots + 1024 < kCompactTiles, "the table never fills up");
+  const bool sampling = smp.act != nullptr && src_out != nullptr && base >= smp.min_rows;
+  if (sampling) {
+    unsigned *tab = reinterpret_cast<unsigned *>(toff);
+    for (int i = tid; i < kCompactTiles; i += 1024) tab[i] = kDictEmpty;
+    if (tid == 0) distinct = 0;
+    __syncthreads();
+    for (int i = tid; i < kSampleValues; i += 1024) {
+      if (__hip_atomic_load(&distinct, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > kDictSlots) break;
+      const int p = src_out[(int)((long long)i * base / kSampleValues)];
+      const unsigned k = (unsigned)(((unsigned long long)((unsigned)i * 0x9E3779B1u) * (unsigned)smp.N) >> 32);
+      float v;
+      if (smp.rows_major) {
+        v = smp.act[(size_t)p * smp.N + k];
+      } else {
+        const size_t t = (size_t)(p >> 5);
+        const bool stored = !smp.seglive || ((smp.seglive[t * ((smp.N + 31) / 32) + (k >> 5)] >> (k & 31)) & 1u);
+        v = stored ? smp.act[(t * smp.N + k) * 32 + (p & 31)] : 0.0f;
+      }
+      const unsigned key = __float_as_uint(v);
+      for (unsigned h = (key * 0x9E3779B1u) >> 20;; h = (h + 1) & (kCompactTiles - 1)) {
+        const unsigned old = atomicCAS(&tab[h], kDictEmpty, key);
+        if (old == kDictEmpty) atomicAdd(&distinct, 1);
+        if (old == kDictEmpty || old == key) break;
+      }
+    }
+    __syncthreads();
+  }
   if (tid == 0) {
     *count_out = base;
     if (count_out2) *count_out2 = base;
     if (notify) {
-      const unsigned long long flags = (misc[0] != 0 ? 1ull : 0ull) | (misc[kOverflowSlot] != 0 ? 2ull : 0ull);
+      const unsigned long long flags = (misc[0] != 0 ? 1ull : 0ull) | (misc[kOverflowSlot] != 0 ? 2ull : 0ull) |
+                                       (sampling && distinct > kDictSlots ? 4ull : 0ull);
       __hip_atomic_store(notify, (tag << 40) | (flags << 32) | (unsigned long long)(unsigned)base, __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_SYSTEM);
     }
@@ -341,14 +386,14 @@ __global__ __launch_bounds__(256) void k_fill_dead(float *__restrict__ fm, int N
 }
 
 // Copy list positions pos[0..n) of feature-major tiles out as rows: out[i][k] = fm at position
-// pos[i], source k.
+// pos[i], source k. With rowmajor, fm holds whole rows by position instead.
 __global__ __launch_bounds__(256) void k_gather_rows(const float *__restrict__ fm, int N, const int *__restrict__ pos,
-                                                     int n, float *__restrict__ out) {
+                                                     int n, float *__restrict__ out, bool rowmajor) {
   const size_t items = (size_t)n * N;
   for (size_t it = blockIdx.x * (size_t)blockDim.x + threadIdx.x; it < items; it += (size_t)gridDim.x * blockDim.x) {
     const int i = (int)(it / N), k = (int)(it % N);
     const int p = pos[i];
-    out[it] = fm[((size_t)(p >> 5) * N + k) * 32 + (p & 31)];
+    out[it] = rowmajor ? fm[(size_t)p * N + k] : fm[((size_t)(p >> 5) * N + k) * 32 + (p & 31)];
   }
 }
 
@@ -1052,6 +1097,300 @@ __global__ __launch_bounds__(256) void k_layer_gfm(const float *__restrict__ fin
   }
 }
 
+// One layer whose activations are fp32 rows in global memory, for widths up to kSegMaxNeurons: a
+// workgroup takes 4 rows at a time (list positions 4i .. 4i + 3) and stages their values in LDS as
+// [source][4 rows], so that one 16-byte LDS read serves an edge for 4 rows. kSegCap sources fit; a
+// wider layer runs in S = 2 segments, [0, kSegCap) and then [N - kSegCap, N), and the sums of all
+// the workgroup's outputs stay in registers across them (16 outputs x 4 rows per thread). Every
+// column's sources are split between the segments in ascending order, so each sum is the same
+// ascending chain as everywhere; the overlap of the segments lets the loader cut almost every
+// column of 32 sources into 16 + 16. Columns hold any number of sources: the loader sorts them by
+// their groups of 8 terms per segment and pads a block of 64 columns to its longest (padding is
+// (row 0 of the segment, weight +0), a no-op term).
+//   stream: groups of 8 terms of 64 columns, 3 KiB each: [64 lanes] of 8 u16 sources (within the
+//     segment), then [64 lanes] of the first 4 and of the last 4 weights; a wave's groups follow each
+//     other, so the next group is loaded while the current one is summed.
+//   desc[s * nblk + k]: first group and number of groups of column block k in segment s; block k is
+//     taken by wave k % 16 as its output k / 16.
+//   colb[64 k + lane]: the column (kNoColumn: none) and its bias.
+// Bound: the LDS reads (16 lanes at random rows take 3.06 of the cycles that conflict-free ones take, so
+// at most 21 edge-rows per clock and CU) while sums run, 2/3 of the time, then the rows' way in and
+// out, which every CU takes at about the same time. Gathers of 128-byte segments from a resident L2
+// (k_layer_gfm) end at 12, and reach 7.3. 15,000 live rows at 16384 neurons: 1.08 ms per layer against
+// 1.83 for k_layer_gfm; columns of 1 to 48 sources at 10007 neurons, 3000 rows: 0.13 ms against 0.94.
+// Tried: 16-byte loads and stores of the rows (8% slower: their 4-way conflicts in the LDS transposes),
+// staggered starts of the workgroups (2%), LDS reads 3 to 8 terms ahead (5 is best by 1-5%), and columns
+// regrouped at load time for fewer conflicts (2.7% faster, for 10% of the load time).
+// With nsplit > 1 (fewer 4-row groups than CUs) nsplit workgroups share a group's outputs. With
+// nsplit = 1 the workgroup knows which of its rows stay live: dead rows are not written, and the
+// others go through LDS back into column order. map: the row of yin that holds list position p (null:
+// p itself). rownz (layer 0): rows with a nonzero input.
+constexpr int kSegThreads = 1024;
+constexpr int kSegOutputs = 16;                // outputs per thread
+constexpr int kSegMaxNeurons = kSegThreads * kSegOutputs;
+constexpr int kSegCap = 10112;                 // sources in LDS: 158 KiB
+#ifndef SDNN_SEG_AHEAD
+#define SDNN_SEG_AHEAD 5
+#endif
+constexpr int kSegAhead = SDNN_SEG_AHEAD;      // LDS reads in flight ahead of the fmas
+constexpr unsigned kNoColumn = 0x80000000u;
+constexpr int kSegGroupWords = 192;            // uint4 words of a group
+static_assert(2 * kSegCap >= kSegMaxNeurons && kSegCap * 16 + 1024 <= 160 * 1024, "two segments cover the widest layer");
+// f(0), f(1), ..., each with its index as a compile-time constant (arrays indexed by it stay in
+// registers whatever loops f holds)
+template <class F, int... I>
+__device__ __forceinline__ void static_for(F &&f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+// Barrier of a workgroup that orders LDS accesses only: global stores in flight are not waited for.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// 16 times the low (half = 0) or high u16 of u, in one instruction (a word-select on the operand); four
+// holds 4.
+template <int HALF>
+__device__ __forceinline__ unsigned word_times_16(unsigned u, unsigned four) {
+  unsigned r;
+  if constexpr (HALF == 0)
+    asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0"
+        : "=v"(r) : "v"(four), "v"(u));
+  else
+    asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1"
+        : "=v"(r) : "v"(four), "v"(u));
+  return r;
+}
+
+template <int S>
+__global__ __launch_bounds__(kSegThreads) void k_layer_seg(
+    const float *__restrict__ yin, float *__restrict__ yout, int N, const uint4 *__restrict__ stream,
+    const int2 *__restrict__ desc, const uint2 *__restrict__ colb, int nblk, float ymax, const int *__restrict__ map,
+    const int *__restrict__ npos, int nsplit, unsigned *__restrict__ masks, unsigned *__restrict__ spread,
+    int *__restrict__ rownz, const int *__restrict__ ids) {
+  extern __shared__ float4 tile[];  // (the only LDS: the tile starts at address 0, and two words follow it)
+  unsigned &livebits = *reinterpret_cast<unsigned *>(tile + min(N, kSegCap));
+  unsigned &anybits = *(&livebits + 1);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int R = *npos;
+  const int nob = (nblk + 15) / 16;
+  const int opw = (nob + nsplit - 1) / nsplit;
+  const int items = (R + 3) / 4 * nsplit;
+  const char *tb = reinterpret_cast<const char *>(tile);
+  unsigned four = 4u;
+  asm volatile("" : "+v"(four));
+  const std::make_integer_sequence<int, kSegOutputs> outputs{};
+  constexpr int kStage = (kSegCap + kSegThreads - 1) / kSegThreads;  // sources of a segment per thread
+  const int nk = S == 1 ? N : kSegCap;                               // sources of a segment
+  float v[kStage][4];
+  const float *row[4];
+  // the rows of an item (positions past the list repeat the last one; their sums are not stored)
+  auto take_rows = [&](int it) {
+    const int q0 = it / nsplit * 4;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const int p = min(q0 + b, R - 1);
+      // (uniform: the row address stays in scalar registers)
+      row[b] = yin + (size_t)(unsigned)__builtin_amdgcn_readfirstlane(map ? map[p] : p) * (unsigned)N;
+    }
+  };
+  // segment s of those rows, into registers (all of them assigned, so that none is live before)
+  auto load = [&](int s) {
+    const int k0 = s == 0 ? 0 : N - kSegCap;
+    int t = tid;
+    asm volatile("" : "+v"(t));  // (the offsets are formed here, not kept in registers across the sums)
+#pragma unroll
+    for (int u = 0; u < kStage; ++u) {
+      const unsigned k = (unsigned)(k0 + min(u * kSegThreads + t, nk - 1));
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+        v[u][b] = u * kSegThreads < nk
+                      ? *reinterpret_cast<const float *>(reinterpret_cast<const char *>(row[b]) + k * 4u)
+                      : 0.0f;
+    }
+  };
+  if ((int)blockIdx.x >= items) return;  // uniform over the workgroup
+  if (tid == 0) {
+    livebits = 0u;
+    anybits = 0u;
+  }
+  take_rows(blockIdx.x);
+  load(0);
+  for (int item = blockIdx.x; item < items; item += gridDim.x) {
+    const int part = item % nsplit;
+    const int p0 = item / nsplit * 4;
+    const int nvalid = min(4, R - p0);
+    const int o0 = part * opw;
+    const int on = max(0, min(nob - o0, opw));  // outputs of each thread
+    float acc[kSegOutputs][4];
+#pragma unroll
+    for (int o = 0; o < kSegOutputs; ++o)
+#pragma unroll
+      for (int b = 0; b < 4; ++b) acc[o][b] = 0.0f;
+    unsigned any = 0u;
+    uint2 cb[kSegOutputs];  // column and bias of each output
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      // lane o holds the description of this wave's block of output o
+      const int blk = (o0 + lane) * 16 + wave;
+      int2 d = make_int2(0, 0);
+      if (lane < on && blk < nblk) d = desc[s * nblk + blk];
+#pragma unroll
+      for (int u = 0; u < kStage; ++u) {
+        const int k = u * kSegThreads + tid;
+        if (k < nk) tile[k] = make_float4(v[u][0], v[u][1], v[u][2], v[u][3]);
+        if (rownz && k < nk)
+#pragma unroll
+          for (int b = 0; b < 4; ++b) any |= (v[u][b] != 0.0f ? 1u : 0u) << b;
+      }
+      int g = __builtin_amdgcn_readlane(d.x, 0);
+      const uint4 *gp = stream + (size_t)g * kSegGroupWords + lane;
+      uint4 ix = gp[0], w0 = gp[64], w1 = gp[128], jx, u0, u1;
+      lds_barrier();
+      static_for([&](auto oc) {
+        constexpr int o = decltype(oc)::value;
+        if (o >= on) return;
+        // (the descriptions are read here, not hoisted: 32 scalar registers would spill)
+        asm volatile("" : "+v"(d.x), "+v"(d.y));
+        const int ng = __builtin_amdgcn_readlane(d.y, o);
+        const int after = o + 1 < kSegOutputs ? __builtin_amdgcn_readlane(d.x, o + 1) : 0;
+        // the sums of one group, whose lists are in (ix, w0, w1)
+        auto sum = [&](const uint4 &ix, const uint4 &w0, const uint4 &w1) {
+          const unsigned q[4] = {ix.x, ix.y, ix.z, ix.w};
+          const float w[8] = {__uint_as_float(w0.x), __uint_as_float(w0.y), __uint_as_float(w0.z), __uint_as_float(w0.w),
+                              __uint_as_float(w1.x), __uint_as_float(w1.y), __uint_as_float(w1.z), __uint_as_float(w1.w)};
+          // LDS reads kSegAhead terms ahead of their fmas
+          float4 x[kSegAhead];
+          auto rd = [&](int t) {
+            return *reinterpret_cast<const float4 *>(
+                tb + ((t & 1) ? word_times_16<1>(q[t / 2], four) : word_times_16<0>(q[t / 2], four)));
+          };
+#pragma unroll
+          for (int t = 0; t < kSegAhead; ++t) x[t] = rd(t);
+#pragma unroll
+          for (int t = 0; t < 8; ++t) {
+            __builtin_amdgcn_sched_barrier(0);
+            const float4 y = x[t % kSegAhead];
+            acc[o][0] = fmaf(y.x, w[t], acc[o][0]);
+            acc[o][1] = fmaf(y.y, w[t], acc[o][1]);
+            acc[o][2] = fmaf(y.z, w[t], acc[o][2]);
+            acc[o][3] = fmaf(y.w, w[t], acc[o][3]);
+            if (t + kSegAhead < 8) x[t % kSegAhead] = rd(t + kSegAhead);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        };
+        // a group's lists are loaded while the one before it is summed (the last one's successor is the
+        // first group of the wave's next block); two register sets in turn
+        auto lists = [&](int gi, uint4 &ix, uint4 &w0, uint4 &w1) {
+          const uint4 *np = stream + (size_t)(unsigned)gi * kSegGroupWords;
+          ix = np[lane];
+          w0 = np[lane + 64];
+          w1 = np[lane + 128];
+          mem_fence_compiler();
+        };
+        int i = 0;
+        for (; i + 1 < ng; i += 2) {
+          lists(g + 1, jx, u0, u1);
+          sum(ix, w0, w1);
+          g = i + 2 < ng ? g + 2 : after;
+          lists(g, ix, w0, w1);
+          sum(jx, u0, u1);
+        }
+        if (i < ng) {
+          g = after;
+          lists(g, jx, u0, u1);
+          sum(ix, w0, w1);
+          ix = jx;
+          w0 = u0;
+          w1 = u1;
+        }
+      }, outputs);
+      // a wave that is done loads what comes next while the others finish
+      if (s + 1 < S) {
+        load(s + 1);
+      } else {
+        const uint2 *cp = colb + (size_t)o0 * kSegThreads;
+        static_for([&](auto oc) {
+          constexpr int o = decltype(oc)::value;
+          cb[o] = o < on ? cp[(unsigned)(o * kSegThreads + tid)] : make_uint2(kNoColumn, 0u);
+        }, outputs);
+      }
+      mem_fence_compiler();
+      lds_barrier();  // every read of the segment is done
+    }
+    unsigned lm = 0u;
+    static_for([&](auto oc) {
+      constexpr int o = decltype(oc)::value;
+      if (o >= on) return;
+      if (cb[o].x != kNoColumn) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          acc[o][b] = activate(acc[o][b], __uint_as_float(cb[o].y), ymax);
+          lm |= (acc[o][b] > 0.0f ? 1u : 0u) << b;
+        }
+        if (nsplit > 1) {
+#pragma unroll
+          for (int b = 0; b < 4; ++b)
+            if (b < nvalid) yout[(size_t)(p0 + b) * N + cb[o].x] = acc[o][b];
+        }
+      }
+    }, outputs);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const unsigned l1 = __ballot((lm >> b) & 1u) != 0ull ? 1u << b : 0u;
+      const unsigned a1 = rownz && __ballot((any >> b) & 1u) != 0ull ? 1u << b : 0u;
+      if (lane == 0 && l1) atomicOr(&livebits, l1);
+      if (lane == 0 && a1) atomicOr(&anybits, a1);
+    }
+    lds_barrier();
+    const unsigned live = livebits & ((1u << nvalid) - 1u);
+    const unsigned nonzero = anybits;
+    const bool write = nsplit == 1 && live != 0u;
+    const int H = S == 1 ? N : (N + 1) / 2;  // columns that go through LDS at a time
+    auto to_tile = [&](int c0, int nc) {
+      static_for([&](auto oc) {
+        constexpr int o = decltype(oc)::value;
+        if (o >= on) return;
+        const unsigned c = cb[o].x - (unsigned)c0;  // (kNoColumn stays past every width)
+        if (c < (unsigned)nc) tile[c] = make_float4(acc[o][0], acc[o][1], acc[o][2], acc[o][3]);
+      }, outputs);
+    };
+    auto from_tile = [&](int c0, int nc) {
+      for (int k = tid; k < nc; k += kSegThreads) {
+        const float4 y = tile[k];
+        float *dst = yout + (size_t)p0 * N + c0 + k;
+        if (live & 1u) dst[0] = y.x;
+        if (live & 2u) dst[(size_t)N] = y.y;
+        if (live & 4u) dst[(size_t)2 * N] = y.z;
+        if (live & 8u) dst[(size_t)3 * N] = y.w;
+      }
+    };
+    if (write && S == 2) {
+      to_tile(0, H);
+      lds_barrier();
+      from_tile(0, H);
+      lds_barrier();
+    }
+    const int c1 = S == 1 ? 0 : H;
+    if (write) to_tile(c1, N - c1);
+    // the next item's first segment is loaded while this one's last outputs go out
+    take_rows(min(item + (int)gridDim.x, items - 1));
+    load(0);
+    mem_fence_compiler();
+    lds_barrier();
+    if (write) from_tile(c1, N - c1);
+    if (tid == 0) {
+      livebits = 0u;
+      anybits = 0u;
+      if (live) or_mask(masks, spread, p0 >> 5, live << (p0 & 31));
+    }
+    if (rownz && tid < nvalid && ((nonzero >> tid) & 1u)) rownz[ids[p0 + tid]] = 1;
+    lds_barrier();
+  }
+}
+
 // Progress word of few-tile layers, stored by workgroup 0 of each launch into coherent host memory:
 // run generation (16 bits) | layer of the launch (20 bits) | live count of the previous layer (28
 // bits; all ones when this launch did not count it). The host reads it to follow the device
@@ -1395,7 +1734,10 @@ __device__ __forceinline__ unsigned dict_code_slow(unsigned key, unsigned *dlk, 
     }
     h = (h + 1) & (HASH - 1);
   }
-  *overflow = 1;
+  // device scope, as it is read (a plain store would stay in this XCD's L2 until the kernel ends), and
+  // once: a store per lane that fails took a failed repack from 0.10 to 0.29 ms at 65536 neurons
+  if (!__hip_atomic_load(overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    __hip_atomic_store(overflow, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return 0;
 }
 // The cache's answer for `key`: *code, and whether it was there.
@@ -1792,7 +2134,7 @@ __global__ void k_report_overflow(const int *__restrict__ overflow, unsigned lon
 
 // After a compaction of the global-tile path: move the live positions of a layer's output tiles
 // into fresh tiles, dst[t][k][b] = the value at list position src[32t + b] of the source tiles
-// (tile src / 32, slot src % 32), for positions below *npos; zero past it. A work item is one new
+// (tile src / 32, slot src % 32; the position itself with src null), for positions below *npos; zero past it. A work item is one new
 // tile and kRepackSources sources. The new tile's rows come from at most 32 old tiles (src is
 // ascending); for each of them, 8 lanes read a source's whole 128-byte segment (one 16-byte load
 // each), keep the rows the new tile takes, and place them in an LDS stage from which the new
@@ -1800,13 +2142,16 @@ __global__ void k_report_overflow(const int *__restrict__ overflow, unsigned lon
 // set, an old segment whose bit there is clear was never stored (all its rows are zero) and is not
 // read. With cols set (tiles of a layer that computed only the columns cols[0..ncols); seglive is
 // then null), only those sources are moved.
-// With CB = 1 the new tiles are written as one-byte dictionary codes instead, in code tiles of CR
+// With OUT = kRepackRows the live positions are written as rows instead, dfm[p][k] (no position past
+// *npos), for k_layer_seg; cols must be null.
+// With OUT = kRepackCodes the new tiles are written as one-byte dictionary codes, in code tiles of CR
 // positions as k_encode writes them (dcodes; cols must be null): the repack and the encoding of the
 // next layer's inputs in one pass. Every position of the last code tile is written (code 0 past
 // *npos). A full dictionary sets *overflow, and the workgroups stop at their next work item (the
 // caller then repacks the fp32 tiles).
 constexpr int kRepackSources = 256;
-template <int CB = 0, int CR = 32>
+constexpr int kRepackTiles = 0, kRepackCodes = 1, kRepackRows = 2;
+template <int OUT = kRepackTiles, int CR = 32>
 __global__ __launch_bounds__(256) void k_repack(const float *__restrict__ sfm, float *__restrict__ dfm, int N,
                                                 const int *__restrict__ src, const int *__restrict__ npos,
                                                 const unsigned *__restrict__ seglive, const int *__restrict__ cols,
@@ -1818,24 +2163,24 @@ __global__ __launch_bounds__(256) void k_repack(const float *__restrict__ sfm, f
   __shared__ int nold;
   __shared__ unsigned segw[32];        // seglive words of the old tiles for the current 32 sources
   __shared__ float stage[32][33];
-  static_assert(CB == 0 || CB == 1, "fp32 tiles or one-byte codes");
-  constexpr int CE = CB > 0 ? kCacheEntries : 2;
-  __shared__ __align__(8) unsigned dlk[CE];  // the dictionary's LDS cache (CB > 0)
+  constexpr bool CODES = OUT == kRepackCodes;
+  constexpr int CE = CODES ? kCacheEntries : 2;
+  __shared__ __align__(8) unsigned dlk[CE];  // the dictionary's LDS cache (CODES)
   __shared__ __align__(8) unsigned dlc[CE];
   __shared__ int stop;
-  if constexpr (CB > 0) {
+  if constexpr (CODES) {
     for (int i = threadIdx.x; i < CE; i += blockDim.x) dlk[i] = kDictEmpty;
   }
   const int R = *npos;
   // (codes: every 32-position tile of the last code tile, those past the list all zero)
-  const int ntiles = CB > 0 ? (R + CR - 1) / CR * (CR / 32) : (R + 31) / 32;
+  const int ntiles = CODES ? (R + CR - 1) / CR * (CR / 32) : (R + 31) / 32;
   const int nkc = (ncols + kRepackSources - 1) / kRepackSources;
   const int tid = threadIdx.x, kk = tid >> 3, q = tid & 7;
   const int NW = (N + 31) / 32;
   for (int item = blockIdx.x; item < ntiles * nkc; item += gridDim.x) {
     const int t = item / nkc, k0 = (item % nkc) * kRepackSources;
     const int nb = max(0, min(32, R - t * 32));
-    if constexpr (CB > 0) {
+    if constexpr (CODES) {
       if (tid == 0) stop = __hip_atomic_load(overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       __syncthreads();
       if (stop) return;  // uniform: every thread read the one word
@@ -1843,7 +2188,7 @@ __global__ __launch_bounds__(256) void k_repack(const float *__restrict__ sfm, f
     if (tid == 0) {
       int n = 0, last = -1;
       for (int b = 0; b < nb; ++b) {
-        const int sp = src[t * 32 + b];
+        const int sp = src ? src[t * 32 + b] : t * 32 + b;
         const int ot = sp >> 5;
         if (ot != last) {
           otile[n] = ot;
@@ -1891,7 +2236,7 @@ __global__ __launch_bounds__(256) void k_repack(const float *__restrict__ sfm, f
         }
       }
       __syncthreads();
-      if constexpr (CB > 0) {
+      if constexpr (CODES) {
         if (k < N) {
           // codes of rows 4q .. 4q + 3 of this 32-position tile, at its place in its code tile
           unsigned c[4];
@@ -1904,6 +2249,20 @@ __global__ __launch_bounds__(256) void k_repack(const float *__restrict__ sfm, f
           }
           unsigned char *d = dcodes + ((size_t)(t / (CR / 32)) * N + k) * CR + (t % (CR / 32)) * 32 + 4 * q;
           *reinterpret_cast<unsigned *>(d) = c[0] | (c[1] << 8) | (c[2] << 16) | (c[3] << 24);
+        }
+      } else if constexpr (OUT == kRepackRows) {
+        // row kk of the tile, sources 4q .. 4q + 3 of the 32
+        const int ks = k0 + kb + 4 * q;
+        if (kk < nb) {
+          float *d = dfm + (size_t)(t * 32 + kk) * N + ks;
+          if ((N & 3) == 0 && ks < N) {
+            *reinterpret_cast<float4 *>(d) =
+                make_float4(stage[4 * q][kk], stage[4 * q + 1][kk], stage[4 * q + 2][kk], stage[4 * q + 3][kk]);
+          } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+              if (ks + c < N) d[c] = stage[4 * q + c][kk];
+          }
         }
       } else if (k < N) {
         *reinterpret_cast<float4 *>(dfm + ((size_t)t * N + k) * 32 + 4 * q) =
@@ -2553,7 +2912,108 @@ struct LayerDev {
   const float *gw8[3] = {};  // the weights of gell16's positions (layers with w8)
   int D = 0;
   bool dedup_ok = false;
+  // global-tile path, widths up to kSegMaxNeurons, without the equal-value kernels: the layer's
+  // columns as k_layer_seg reads them
+  const uint4 *seg = nullptr;
+  const int2 *segdesc = nullptr;
+  const uint2 *segcol = nullptr;
 };
+
+// A layer's columns in the order and grouping of k_layer_seg: blocks of 64 columns, each with its
+// groups of 8 terms per segment.
+struct SegPack {
+  std::vector<uint32_t> col;      // column of position p, kNoColumn past the last
+  std::vector<int2> desc;         // [S][blocks]: first group, groups
+  size_t groups = 0;
+};
+int seg_segments(int N) { return N <= kSegCap ? 1 : 2; }
+int seg_blocks(int N) { return (N + 63) / 64; }
+int seg_positions(int N) { return (int)align_up((size_t)N, kSegThreads); }
+
+// src(j, i): source i of column j, ascending; deg(j): its number of sources.
+template <class Src, class Deg>
+SegPack seg_order(int N, Src src, Deg deg, std::vector<uint16_t> *first) {
+  const int S = seg_segments(N), nb = seg_blocks(N);
+  // terms of column j in segment 0 (*first) and groups of 8 per segment: sources below N - kSegCap
+  // have to be in segment 0, those from kSegCap in segment 1, and the cut is free between them: the
+  // fewest groups, then the most even cut (one class of columns is one run length for its waves)
+  std::vector<uint32_t> key((size_t)N);
+  first->resize((size_t)N);
+  for (int j = 0; j < N; ++j) {
+    const int d = deg(j);
+    int n0 = d;
+    if (S == 2) {
+      int lo = 0, hi = 0;
+      while (lo < d && src(j, lo) < N - kSegCap) ++lo;
+      hi = lo;
+      while (hi < d && src(j, hi) < kSegCap) ++hi;
+      int best = 1 << 30;
+      auto take = [&](int n) {
+        const int a = (n + 7) / 8, b = (d - n + 7) / 8;
+        const int cost = (a + b) * 4096 + std::abs(a - b);
+        if (cost < best) { best = cost; n0 = n; }
+      };
+      take(lo);
+      take(hi);
+      for (int n = (lo + 7) / 8 * 8; n <= hi; n += 8) take(n);
+      for (int n = hi; n >= lo && n > hi - 8; --n)  // the cuts that fill segment 1's last group
+        if ((d - n) % 8 == 0) take(n);
+    }
+    (*first)[(size_t)j] = (uint16_t)n0;
+    const uint32_t a = (uint32_t)(n0 + 7) / 8, b = (uint32_t)(d - n0 + 7) / 8;
+    key[(size_t)j] = (a + b) * 1024u + a;
+  }
+  // longest columns first (blocks go round the waves, so every wave gets some), stable, so that equal
+  // columns stay in order and their outputs are consecutive
+  std::vector<int32_t> order((size_t)N);
+  for (int j = 0; j < N; ++j) order[(size_t)j] = j;
+  if (!std::all_of(key.begin(), key.end(), [&](uint32_t k) { return k == key[0]; }))
+    std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return key[(size_t)x] > key[(size_t)y]; });
+  SegPack p;
+  p.col.assign((size_t)seg_positions(N), kNoColumn);
+  for (int i = 0; i < N; ++i) p.col[(size_t)i] = (uint32_t)order[(size_t)i];
+  p.desc.resize((size_t)S * nb);
+  // a wave's groups in the order it sums them: segment by segment, its blocks in turn (an empty
+  // block's first group is that of the next one, which the kernel loads ahead)
+  for (int w = 0; w < 16; ++w)
+    for (int sg = 0; sg < S; ++sg)
+      for (int k = w; k < nb; k += 16) {
+        uint32_t n = 0;
+        for (int c = 0; c < 64; ++c) {
+          const uint32_t j = p.col[(size_t)k * 64 + c];
+          if (j == kNoColumn) continue;
+          const uint32_t a = key[j] % 1024u;
+          n = std::max(n, sg == 0 ? a : key[j] / 1024u - a);
+        }
+        p.desc[(size_t)sg * nb + k] = make_int2((int)p.groups, (int)n);
+        p.groups += n;
+      }
+  return p;
+}
+
+// The groups of seg_order's layer, kSegGroupWords uint4 each, zeroed beforehand by the caller.
+template <class Src, class Val, class Deg>
+void seg_fill(int N, const SegPack &p, const std::vector<uint16_t> &first, Src src, Val val, Deg deg, uint32_t *out) {
+  const int S = seg_segments(N), nb = seg_blocks(N);
+  for (int k = 0; k < nb; ++k)
+    for (int c = 0; c < 64; ++c) {
+      const uint32_t uj = p.col[(size_t)k * 64 + c];
+      if (uj == kNoColumn) continue;
+      const int j = (int)uj;
+      for (int sg = 0; sg < S; ++sg) {
+        const int i0 = sg == 0 ? 0 : first[(size_t)j], i1 = sg + 1 == S ? deg(j) : first[(size_t)j];
+        const int base = sg == 0 ? 0 : N - kSegCap;
+        uint32_t *g = out + (size_t)p.desc[(size_t)sg * nb + k].x * kSegGroupWords * 4;
+        for (int i = i0; i < i1; ++i) {
+          const int t = (i - i0) % 8;
+          uint32_t *b = g + (size_t)((i - i0) / 8) * kSegGroupWords * 4;
+          reinterpret_cast<uint16_t *>(b + c * 4)[t] = (uint16_t)(src(j, i) - base);
+          const float v = val(j, i);
+          std::memcpy(b + 256 + (t / 4) * 256 + c * 4 + t % 4, &v, sizeof(float));
+        }
+      }
+    }
+}
 
 // Layers (from layer 0) that get an LDS row placement: the per-layer kernel runs the first layers
 // of a batch, before the fused launch takes over.
@@ -2672,6 +3132,7 @@ struct sdnn_net {
   std::vector<int32_t> layer_kernel, layer_launches;  // per layer of the last infer (sdnn_layer_info)
   const float *final_y = nullptr;   // path 0: final activations, row-major by row id
   const float *final_fm = nullptr;  // path 1: final activation tiles; live row i is at position src[final_list][i]
+  bool final_rows_major = false;    // ... or rows by position (k_layer_seg's outputs)
   int32_t *pinned = nullptr; // read-back slots (0-3: polling ring, 6: input-not-binary flag, 7: exact count)
   // progress word of few-tile layers, in coherent host memory written by the device (see
   // progress_word); progress_dev is its device address
@@ -2866,6 +3327,38 @@ hipError_t launch_gfm(sdnn_net *net, const LayerDev &ld, const float *fin, float
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+// A layer on fp32 rows (see k_layer_seg): reads row map[p] of yin for list position p (null: row p),
+// writes row p of yout.
+hipError_t launch_seg(sdnn_net *net, const LayerDev &ld, const float *yin, float *yout, const int *map, const int *npos,
+                      int64_t rows, unsigned *masks, int *rownz, const int *ids) {
+  static std::atomic<bool> configured{false};
+  if (!configured.load(std::memory_order_acquire)) {
+    for (const void *k : {reinterpret_cast<const void *>(&k_layer_seg<1>), reinterpret_cast<const void *>(&k_layer_seg<2>)}) {
+      const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                               (kSegCap + 1) * (int)sizeof(float4));
+      if (e != hipSuccess) return e;
+    }
+    configured.store(true, std::memory_order_release);
+  }
+  const int nblk = seg_blocks(net->N), nob = (nblk + 15) / 16;
+  const int64_t quads = (rows + 3) / 4;
+  // fewer 4-row groups than CUs: split their outputs until the CUs are taken
+  int nsplit = 1;
+  if (quads < net->cus) nsplit = (int)std::min<int64_t>(nob, net->cus / std::max<int64_t>(1, quads));
+  nsplit = std::max(1, nsplit);
+  const int opw = (nob + nsplit - 1) / nsplit;
+  nsplit = (nob + opw - 1) / opw;
+  const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(net->cus, quads * nsplit));
+  const size_t lds = ((size_t)std::min(net->N, kSegCap) + 1) * sizeof(float4);  // (+ two words)
+  if (seg_segments(net->N) == 1)
+    hipLaunchKernelGGL(k_layer_seg<1>, dim3(grid), dim3(kSegThreads), lds, net->stream, yin, yout, net->N, ld.seg,
+                       ld.segdesc, ld.segcol, nblk, net->ymax, map, npos, nsplit, masks, net->spread, rownz, ids);
+  else
+    hipLaunchKernelGGL(k_layer_seg<2>, dim3(grid), dim3(kSegThreads), lds, net->stream, yin, yout, net->N, ld.seg,
+                       ld.segdesc, ld.segcol, nblk, net->ymax, map, npos, nsplit, masks, net->spread, rownz, ids);
+  return hipGetLastError();
 }
 
 hipError_t launch_to_fm(sdnn_net *net, const float *y, float *fm, const int *ids, const int *count, int *rownz) {
@@ -3451,6 +3944,62 @@ sdnn_status sdnn_load_layers(sdnn_net *net, int32_t l0, int32_t nl, const int64_
       }
     }
   }
+  if (net->path == 1 && N <= kSegMaxNeurons && !net->equal_value_kernels) {
+    // the layers as k_layer_seg reads them: groups, descriptions and column order of each
+    std::vector<SegPack> packs((size_t)nl);
+    std::vector<std::vector<uint16_t>> first((size_t)nl);
+    auto src_of = [&](int32_t i) {
+      return [row_idx, cp = col_ptr + (size_t)i * (N + 1)](int j, int t) { return row_idx[cp[j] + t]; };
+    };
+    auto deg_of = [&](int32_t i) {
+      return [cp = col_ptr + (size_t)i * (N + 1)](int j) { return (int)(cp[j + 1] - cp[j]); };
+    };
+    auto val_of = [&](int32_t i) {
+      return [val, cp = col_ptr + (size_t)i * (N + 1)](int j, int t) { return val[cp[j] + t]; };
+    };
+    parallel_for(nl, [&](int32_t i) { packs[(size_t)i] = seg_order(N, src_of(i), deg_of(i), &first[(size_t)i]); });
+    // (one more group after each layer's: the kernel loads one ahead)
+    std::vector<size_t> off((size_t)nl + 1, 0);
+    for (int32_t i = 0; i < nl; ++i) off[(size_t)i + 1] = off[(size_t)i] + packs[(size_t)i].groups + 1;
+    const size_t gbytes = off[(size_t)nl] * kSegGroupWords * sizeof(uint4);
+    const size_t dwords = packs[0].desc.size(), cwords = (size_t)seg_positions(N);
+    const size_t dbytes = align_up((size_t)nl * dwords * sizeof(int2), 256);
+    std::vector<uint32_t> hg;
+    std::vector<char> hd;
+    try {
+      hg.assign(gbytes / sizeof(uint32_t), 0u);
+      hd.resize(dbytes + (size_t)nl * cwords * sizeof(uint2));
+    } catch (...) {
+      return fail(SDNN_ENOMEM, "out of host memory packing %zu bytes", gbytes);
+    }
+    parallel_for(nl, [&](int32_t i) {
+      const SegPack &p = packs[(size_t)i];
+      seg_fill(N, p, first[(size_t)i], src_of(i), val_of(i), deg_of(i),
+               hg.data() + off[(size_t)i] * kSegGroupWords * 4);
+      std::memcpy(hd.data() + (size_t)i * dwords * sizeof(int2), p.desc.data(), dwords * sizeof(int2));
+      uint2 *cb = reinterpret_cast<uint2 *>(hd.data() + dbytes) + (size_t)i * cwords;
+      for (size_t q = 0; q < cwords; ++q) {
+        uint32_t b = 0u;
+        if (p.col[q] != kNoColumn) std::memcpy(&b, &bias[(size_t)i * N + p.col[q]], sizeof(uint32_t));
+        cb[q] = make_uint2(p.col[q], b);
+      }
+    });
+    char *mg = nullptr;
+    e = hipMalloc(reinterpret_cast<void **>(&mg), gbytes + hd.size());
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      return fail(SDNN_ENOMEM, "hipMalloc of %zu bytes failed: %s", gbytes + hd.size(), hipGetErrorString(e));
+    }
+    net->allocations.push_back(mg);
+    HIP_OR_POISON(net, hipMemcpy(mg, hg.data(), gbytes, hipMemcpyHostToDevice));
+    HIP_OR_POISON(net, hipMemcpy(mg + gbytes, hd.data(), hd.size(), hipMemcpyHostToDevice));
+    for (int32_t i = 0; i < nl; ++i) {
+      LayerDev &ld = net->layers[(size_t)l0 + i];
+      ld.seg = reinterpret_cast<const uint4 *>(mg) + off[(size_t)i] * kSegGroupWords;
+      ld.segdesc = reinterpret_cast<const int2 *>(mg + gbytes) + (size_t)i * dwords;
+      ld.segcol = reinterpret_cast<const uint2 *>(mg + gbytes + dbytes) + (size_t)i * cwords;
+    }
+  }
   {
     // 16-bit source indices in groups of 8 per output ([4][N][8] u16, one 16-byte load per group):
     // every layer with 32 sources per column on widths staged in LDS, with its weights grouped the
@@ -3808,6 +4357,7 @@ hipError_t poll_step(sdnn_net *net, PollRing &ring, int32_t l, int32_t idx, int6
 struct Report {
   int64_t count = 0;
   bool nonbinary = false, overflow = false;
+  bool many = false;  // the layer's outputs take more values than the one-byte dictionary holds
 };
 
 // Tag for the next reporting compaction (24 bits, never 0: the word starts at 0).
@@ -3828,6 +4378,7 @@ hipError_t wait_report(sdnn_net *net, unsigned long long tag, const int *count_d
       r->count = (int64_t)(w & 0xffffffffull);
       r->nonbinary = ((w >> 32) & 1ull) != 0;
       r->overflow = ((w >> 33) & 1ull) != 0;
+      r->many = ((w >> 34) & 1ull) != 0;
       return hipSuccess;
     }
     if ((it & 4095u) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::seconds(2)) break;
@@ -3842,6 +4393,7 @@ hipError_t wait_report(sdnn_net *net, unsigned long long tag, const int *count_d
   r->count = v[0];
   r->nonbinary = v[1] != 0;
   r->overflow = v[2] != 0;
+  r->many = false;
   return e;
 }
 
@@ -3877,7 +4429,7 @@ sdnn_status infer_lds(sdnn_net *net, const float *y0, int M) {
       // the final list: positions still live after the last layer (bits per 32 positions)
       hipLaunchKernelGGL(k_compact, dim3(1), dim3(1024), 0, s, net->masks, 32, net->ids[cur], net->ids[cur ^ 1],
                          (int *)nullptr, net->counts + l, net->counts + net->L, (int *)nullptr, (const int *)nullptr,
-                         (unsigned long long *)nullptr, 0ull);
+                         (unsigned long long *)nullptr, 0ull, CompactSample{});
       HIP_OR_POISON(net, hipGetLastError());
       cur ^= 1;
       net->layers_run = net->L;
@@ -3915,7 +4467,7 @@ sdnn_status infer_lds(sdnn_net *net, const float *y0, int M) {
     const unsigned long long tag = next_report_tag(net);
     hipLaunchKernelGGL(k_compact, dim3(1), dim3(1024), 0, s, net->masks, mask_rows, net->ids[cur], net->ids[cur ^ 1],
                        (int *)nullptr, net->counts + l, net->counts + l + 1, (int *)nullptr, net->misc,
-                       net->notify_dev, tag);
+                       net->notify_dev, tag, CompactSample{});
     HIP_OR_POISON(net, hipGetLastError());
     cur ^= 1;
     yin = yout;
@@ -3953,7 +4505,15 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
   bool fin_codes = false, fout_codes = false;  // the tiles hold dictionary codes
   bool fin_wide = false;  // fin's codes are two bytes (k_encode<64, 2>), else one
   bool wide_ok = true;    // a two-byte encoding is worth trying
-  bool next_tried = false;     // the repack after this layer tried one-byte codes for the next layer
+  // fp32 rows instead of tiles (k_layer_seg): row p of fin, or row fin_map[p], is list position p
+  bool fin_rows = false, fout_rows = false;
+  const int *fin_map = nullptr;
+  // a layer of `rows` live rows runs on rows: more than one round of tiles, or columns of other than 32
+  // sources (few-tile layers have kernels for 32 only)
+  auto seg_layer = [&](int32_t layer, int64_t rows) {
+    return layer < net->L && net->layers[(size_t)layer].seg && (rows > one_round || net->layers[(size_t)layer].K != 32);
+  };
+  bool next_tried = false;     // the next layer's one-byte codes were tried, or cannot fit
   bool repacked_codes = false;  // ... and wrote them (else fp32 tiles)
   int last_list = 0;
   bool compacted = true;   // the last layer run has been followed by a compaction
@@ -3996,9 +4556,11 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
   bool bits_route = false;  // layer 0 went to the bit-tile kernels (unless the report says otherwise)
   int32_t l = 0;
   for (; l < net->L && live_bound > 0; ++l) {
-    const bool small = l > 0 && P <= one_round;
+    const bool few = l > 0 && P <= one_round;
+    const bool small = few && !fin_rows;
     bool reported = false;  // this layer's launch writes the progress word
     fout_codes = false;
+    fout_rows = false;
     // the columns fout holds, when this layer computed one column per group of equal columns
     const LayerDev &lcur = net->layers[(size_t)l];
     const bool ocols_on = lcur.K == 32 && lcur.src16 && lcur.cols && lcur.dedup_ok;
@@ -4006,7 +4568,7 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
     bool spread_used = false;  // this layer's liveness is in the spread words
     bool seglive_out = false;  // fout's all-zero segments were skipped (net->seglive says which)
     unsigned *mk = masks_for(l);
-    const bool rec = net->profiling && (net->prof_mode == 1 || !small);
+    const bool rec = net->profiling && (net->prof_mode == 1 || !few);
     if (net->profiling) net->prof_rec[(size_t)l] = rec;
     if (rec) HIP_OR_POISON(net, hipEventRecord(net->prof_start[(size_t)l], s));
     bool encoded = false;  // this layer reads codes that k_encode wrote from fp32 tiles
@@ -4014,7 +4576,7 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
     const bool tried = next_tried;  // the repack before this layer tried one-byte codes (they overflowed)
     next_tried = false;
     repacked_codes = false;
-    if (l > 0 && !fin_codes && compacted && live_bound >= kEncodeMinRows && !net->equal_value_kernels) {
+    if (l > 0 && !fin_codes && !fin_rows && compacted && live_bound >= kEncodeMinRows && !net->equal_value_kernels) {
       // a large layer on fp32 tiles: if its inputs take at most 256 distinct values (saturated rows
       // do), encode them as one-byte codes into the free buffer and gather those instead (unless the
       // repack before this layer found that they do not fit: tried); else, if
@@ -4068,6 +4630,19 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
         // inputs of one of them fit 256 values (values that grow more varied stay so for a while)
         if (!encoded) wide_ok = false;
       }
+      if (!encoded && seg_layer(l, P)) {
+        // the tiles as rows, into the buffer the encoding left
+        const int64_t items = tiles(P) * ((net->N + kRepackSources - 1) / kRepackSources);
+        const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(net->cus * 8, items));
+        float *rows = reinterpret_cast<float *>(cbuf);
+        hipLaunchKernelGGL((k_repack<kRepackRows, 32>), dim3(grid), dim3(256), 0, s, fin, rows, net->N,
+                           (const int *)nullptr, npos + cur, (const unsigned *)nullptr, (const int *)nullptr, net->N,
+                           (unsigned char *)nullptr, (unsigned *)nullptr, (int *)nullptr);
+        HIP_OR_POISON(net, hipGetLastError());
+        fin = rows;
+        fin_rows = true;
+        fin_map = nullptr;
+      }
     }
     fout = (fin == net->fm[1]) ? net->fm[0] : net->fm[1];
     if (l == 0) {
@@ -4105,6 +4680,13 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
         HIP_OR_POISON(net, net->bitsT == 32
                                ? launch_layer_bits<32>(net, net->layers[0], net->fm[0], fout, npos + cur, fout_codes)
                                : launch_layer_bits<16>(net, net->layers[0], net->fm[0], fout, npos + cur, fout_codes));
+      } else if (ld0.seg) {
+        // straight from the caller's rows
+        HIP_OR_POISON(net, launch_seg(net, ld0, y0, fout, net->ids[cur], npos + cur, P, mk, net->rownz, net->ids[cur]));
+        spread_used = true;
+        fout_rows = true;
+        net->layer_kernel[0] = SDNN_KERNEL_GLOBAL_TILE;
+        net->layer_launches[0] = 1;
       } else {
         HIP_OR_POISON(net, launch_to_fm(net, y0, net->fm[0], net->ids[cur], npos + cur, try_bits ? nullptr : net->rownz));
         HIP_OR_POISON(net, launch_gfm(net, net->layers[0], net->fm[0], fout, npos + cur, tiles(P), mk, nullptr, nullptr,
@@ -4127,6 +4709,12 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
       const int st = code_rows(net->bitsT) / 32;  // fp32 tiles per code tile
       // (with the dictionary resets, encodings and their reports when this layer encoded its inputs)
       net->layer_launches[(size_t)l] = gfm_launches(net, net->layers[(size_t)l], tiles(P), st * 32) + encode_tries;
+    } else if (fin_rows) {
+      HIP_OR_POISON(net, launch_seg(net, lcur, fin, fout, fin_map, npos + cur, P, mk, nullptr, nullptr));
+      spread_used = true;
+      fout_rows = true;
+      net->layer_kernel[(size_t)l] = SDNN_KERNEL_GLOBAL_TILE;
+      net->layer_launches[(size_t)l] = 1 + encode_tries;
     } else {
       // after a layer without compaction, this launch counts that layer's live rows
       const LayerDev &ld = net->layers[(size_t)l];
@@ -4171,7 +4759,11 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
       }
       hipLaunchKernelGGL(k_compact, dim3(1), dim3(1024), 0, s, mk, 32, net->ids[cur], net->ids[cur ^ 1],
                          net->src[cur ^ 1], npos + cur, net->counts + l + 1, npos + (cur ^ 1), net->misc,
-                         tag ? net->notify_dev : nullptr, tag);
+                         tag ? net->notify_dev : nullptr, tag,
+                         CompactSample{tag && !fout_codes && !fout_cols && l + 1 < net->L && !net->equal_value_kernels
+                                           ? fout : nullptr,
+                                       seglive_out ? net->seglive : nullptr, net->N, fout_rows ? 1 : 0,
+                                       (int)kEncodeMinRows});
       last_list = cur ^ 1;
       return hipGetLastError();
     };
@@ -4190,10 +4782,10 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
       int *of = net->misc + kOverflowSlot;
       const int *sp = net->src[cur ^ 1], *np = npos + (cur ^ 1);
       if (cr == 128)
-        hipLaunchKernelGGL((k_repack<1, 128>), dim3(grid), dim3(256), 0, s, fout, (float *)nullptr, net->N, sp, np, sl,
+        hipLaunchKernelGGL((k_repack<kRepackCodes, 128>), dim3(grid), dim3(256), 0, s, fout, (float *)nullptr, net->N, sp, np, sl,
                            (const int *)nullptr, net->N, dc, gd, of);
       else
-        hipLaunchKernelGGL((k_repack<1, 64>), dim3(grid), dim3(256), 0, s, fout, (float *)nullptr, net->N, sp, np, sl,
+        hipLaunchKernelGGL((k_repack<kRepackCodes, 64>), dim3(grid), dim3(256), 0, s, fout, (float *)nullptr, net->N, sp, np, sl,
                            (const int *)nullptr, net->N, dc, gd, of);
       e = hipGetLastError();
       if (e != hipSuccess) return e;
@@ -4208,6 +4800,7 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
     };
     compacted = false;
     bool adopt;
+    bool many = false;  // the outputs do not fit the one-byte dictionary
     if (!small) {
       // a large layer: compact, and wait for its exact count (the next layer is large, so the wait
       // is short relative to it)
@@ -4219,12 +4812,17 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
       if (l == 0 && bits_route && rp.nonbinary) {
         // an input is not 0 or 1: the bit-tile kernel exited at once; layer 0 on fp32 tiles
         fout_codes = false;
-        HIP_OR_POISON(net, launch_to_fm(net, y0, net->fm[0], net->ids[cur], npos + cur, nullptr));
-        HIP_OR_POISON(net, launch_gfm(net, net->layers[0], net->fm[0], fout, npos + cur, tiles(P), mk, nullptr,
-                                      nullptr, nullptr, net->spread));
+        if (lcur.seg) {
+          HIP_OR_POISON(net, launch_seg(net, lcur, y0, fout, net->ids[cur], npos + cur, P, mk, nullptr, nullptr));
+          fout_rows = true;
+        } else {
+          HIP_OR_POISON(net, launch_to_fm(net, y0, net->fm[0], net->ids[cur], npos + cur, nullptr));
+          HIP_OR_POISON(net, launch_gfm(net, net->layers[0], net->fm[0], fout, npos + cur, tiles(P), mk, nullptr,
+                                        nullptr, nullptr, net->spread));
+        }
         spread_used = true;
         net->layer_kernel[0] = SDNN_KERNEL_GLOBAL_TILE;
-        net->layer_launches[0] = 2 + gfm_launches(net, net->layers[0], tiles(P), 0);
+        net->layer_launches[0] = 2 + (lcur.seg ? 1 : gfm_launches(net, net->layers[0], tiles(P), 0));
         tag = next_report_tag(net);
         HIP_OR_POISON(net, compact(tag));
         HIP_OR_POISON(net, wait_report(net, tag, net->counts + l + 1, &rp));
@@ -4241,10 +4839,15 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
         HIP_OR_POISON(net, wait_report(net, tag, net->counts + l + 1, &rp));
       }
       live_bound = std::min<int64_t>(live_bound, rp.count);
-      adopt = live_bound == 0 || tiles(live_bound) * 20 <= tiles(P) * 19;
+      many = rp.many;
+      // rows move on to the compacted list by its map alone; tiles become rows in the repack
+      adopt = live_bound == 0 || tiles(live_bound) * 20 <= tiles(P) * 19 || fout_rows ||
+              (!fout_codes && seg_layer(l + 1, live_bound));
     } else {
-      adopt = tiles(live_bound) < tiles(P);
+      adopt = tiles(live_bound) < tiles(P) || seg_layer(l + 1, live_bound);
     }
+    next_tried = many;
+    bool next_rows = false;
     if (adopt && live_bound > 0 && l + 1 < net->L) {
       if (!compacted) HIP_OR_POISON(net, compact());
       compacted = true;
@@ -4254,7 +4857,18 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
                                        : tiles(live_bound) * (((fout_cols ? lcur.D : net->N) + kRepackSources - 1) /
                                                               kRepackSources);
       const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(net->cus * 8, items));
-      if (fout_codes && cr == 128)
+      const bool codes_fit = live_bound >= kEncodeMinRows && !net->equal_value_kernels && !many;  // (perhaps)
+      float *next = dst;
+      if (fout_rows) {
+        if (seg_layer(l + 1, live_bound) && !codes_fit) {
+          next_rows = true;
+          next = fout;
+          fin_map = net->src[cur ^ 1];
+        } else {
+          // few rows go on in tiles, and the encoder reads tiles
+          HIP_OR_POISON(net, launch_to_fm(net, fout, dst, net->src[cur ^ 1], npos + (cur ^ 1), nullptr));
+        }
+      } else if (fout_codes && cr == 128)
         hipLaunchKernelGGL(k_repack_u8<128>, dim3(grid), dim3(256), 0, s, reinterpret_cast<const unsigned char *>(fout),
                            reinterpret_cast<unsigned char *>(dst), net->N, net->src[cur ^ 1], npos + (cur ^ 1));
       else if (fout_codes)
@@ -4265,18 +4879,24 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
         // the repack writes one-byte codes itself, and falls back to fp32 tiles when they overflow
         // (two-byte codes are then tried by k_encode from the fp32 tiles: written by the repack
         // they measured slower, 30.9 ms per step against 30.4 at 65536 neurons and 60,000 inputs)
-        if (live_bound >= kEncodeMinRows && !net->equal_value_kernels && !fout_cols) {
+        if (codes_fit && !fout_cols) {
           next_tried = true;
           HIP_OR_POISON(net, repack_codes(dst));
           if (repacked_codes) wide_ok = true;
         }
-        if (!repacked_codes)
-          hipLaunchKernelGGL((k_repack<0, 32>), dim3(grid), dim3(256), 0, s, fout, dst, net->N, net->src[cur ^ 1],
+        if (!repacked_codes && seg_layer(l + 1, live_bound)) {
+          next_rows = true;
+          fin_map = nullptr;
+          hipLaunchKernelGGL((k_repack<kRepackRows, 32>), dim3(grid), dim3(256), 0, s, fout, dst, net->N,
+                             net->src[cur ^ 1], npos + (cur ^ 1), seglive_out ? net->seglive : nullptr,
+                             (const int *)nullptr, net->N, (unsigned char *)nullptr, (unsigned *)nullptr, (int *)nullptr);
+        } else if (!repacked_codes)
+          hipLaunchKernelGGL((k_repack<kRepackTiles, 32>), dim3(grid), dim3(256), 0, s, fout, dst, net->N, net->src[cur ^ 1],
                              npos + (cur ^ 1), seglive_out ? net->seglive : nullptr, fout_cols,
                              fout_cols ? lcur.D : net->N, (unsigned char *)nullptr, (unsigned *)nullptr, (int *)nullptr);
       }
       HIP_OR_POISON(net, hipGetLastError());
-      fin = dst;
+      fin = next;
       cur ^= 1;
       P = live_bound;
     } else {
@@ -4289,6 +4909,7 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
       }
       fin = fout;
     }
+    fin_rows = next_rows;
     fin_codes = fout_codes || repacked_codes;  // (one-byte codes: a layer or a repack writes no others)
     fin_wide = false;
     // counts[l] is final once layer l has run (written by a compaction or by layer l's launch)
@@ -4303,7 +4924,7 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
     HIP_OR_POISON(net, finalize_parts());
     hipLaunchKernelGGL(k_compact, dim3(1), dim3(1024), 0, s, masks_for(last), 32, net->ids[cur], net->ids[cur ^ 1],
                        net->src[cur ^ 1], npos + cur, net->counts + last + 1, npos + (cur ^ 1), (const int *)nullptr,
-                       (unsigned long long *)nullptr, 0ull);
+                       (unsigned long long *)nullptr, 0ull, CompactSample{});
     HIP_OR_POISON(net, hipGetLastError());
     last_list = cur ^ 1;
   }
@@ -4311,6 +4932,7 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
   net->final_list = last_list;
   net->final_y = nullptr;
   net->final_fm = (l == net->L && net->L > 0) ? fout : nullptr;
+  net->final_rows_major = fout_rows;
   return SDNN_OK;
 }
 
@@ -4502,7 +5124,8 @@ sdnn_status sdnn_final_rows(sdnn_net *net, const int64_t *ids, int64_t n, float 
     HIP_OR_POISON(net, hipMemcpy(dpos, pos.data() + b0, (size_t)nb * sizeof(int32_t), hipMemcpyHostToDevice));
     const int64_t items = (int64_t)nb * net->N;
     const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(net->cus * 8, (items + 255) / 256));
-    hipLaunchKernelGGL(k_gather_rows, dim3(grid), dim3(256), 0, net->stream, net->final_fm, net->N, dpos, nb, stage);
+    hipLaunchKernelGGL(k_gather_rows, dim3(grid), dim3(256), 0, net->stream, net->final_fm, net->N, dpos, nb, stage,
+                       net->final_rows_major);
     HIP_OR_POISON(net, hipGetLastError());
     HIP_OR_POISON(net, hipStreamSynchronize(net->stream));
     std::vector<float> rows((size_t)nb * net->N);

@@ -1,0 +1,119 @@
+"""The layer kernel on fp32 rows (k_layer_seg, widths up to 16384 past the LDS tiles) against the oracle: one
+and two LDS segments at their edges, the split of a column's sources between the segments, shared
+outputs for few rows, and the ways its rows come from and go to the tile kernels."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from tests.gpu_util import GpuNet, assert_parity, log, oracle_run
+
+pytestmark = pytest.mark.gpu
+
+CAP = 10112  # sources of one LDS segment
+
+
+def run(n, layers, y0):
+    gpu = GpuNet(n, len(layers))
+    for l, (cp, ri, v, b) in enumerate(layers):
+        gpu.load(l, cp, ri, v, b)
+    cats = gpu.run(y0)
+    o = oracle_run(y0, layers)
+    assert_parity(gpu, o, cats)
+    return gpu, cats
+
+
+def csc(rng, n, columns, scale):
+    """A layer of the given columns (each a set of sources)."""
+    cp = np.zeros(n + 1, np.int64)
+    cp[1:] = np.cumsum([len(c) for c in columns])
+    ri = np.concatenate([np.sort(np.asarray(c, np.int32)) for c in columns] + [np.empty(0, np.int32)]).astype(np.int32)
+    return cp, ri, (rng.random(ri.size) * scale).astype(np.float32)
+
+
+def layer(rng, n, kind):
+    if kind == "ragged":  # any number of sources, none and one among them
+        deg = rng.integers(0, 49, size=n)
+        deg[:3] = (0, 1, 100)
+        cols = [rng.choice(n, size=d, replace=False) for d in deg]
+        scale = 0.16
+    elif kind == "one-sided":  # every source at one end: no cut of 16 and 16 exists
+        cols = [rng.choice(min(n, 600), size=32, replace=False) + (n - min(n, 600) if j % 2 else 0) for j in range(n)]
+        scale = 0.125
+    else:
+        cols = [rng.choice(n, size=32, replace=False) for _ in range(n)]
+        scale = 0.125
+    cp, ri, v = csc(rng, n, cols, scale)
+    return cp, ri, v, rng.uniform(-0.45, -0.35, size=n).astype(np.float32)
+
+
+@pytest.mark.parametrize("n,m,kind", [
+    (4097, 261, "ragged"), (5001, 1, "ragged"), (CAP - 1, 1100, "random"), (CAP, 270, "one-sided"),
+    (CAP + 1, 1030, "random"), (CAP + 1, 3, "ragged"), (12288, 1029, "ragged"), (16383, 300, "one-sided"),
+    (16384, 1301, "random"), (16384, 1, "ragged"),
+])
+def test_rows_layers(n, m, kind):
+    """Three layers from real-valued inputs: layer 0 from the caller's rows, the others from the rows before
+    (or, with 256 rows and fewer and 32 sources per column, from tiles). Rows of several densities,
+    so that some die at every layer and the live rows move; 4-row groups that do not divide the rows."""
+    rng = np.random.default_rng(n + m)
+    dens = rng.uniform(0.35, 1.0, size=(m, 1))
+    y0 = ((rng.random((m, n)) < dens) * rng.random((m, n))).astype(np.float32)
+    if m > 2:
+        y0[m // 2] = 0.0
+    log(f"rows n={n} m={m} {kind}")
+    layers = [layer(rng, n, kind) for _ in range(3)]
+    run(n, layers, y0)
+
+
+@pytest.mark.parametrize("seq", [(32, 40, 32), (40, 32, 40), (40, 40, 32)])
+@pytest.mark.parametrize("m", [90, 700])
+def test_rows_between_tiles(seq, m):
+    """Layers of 32 and of up to 40 sources in turn: few rows go from tiles (32 sources) to rows (any other
+    number) and back, more rows from one-byte codes (binary inputs, 32 sources in layer 0) to rows."""
+    n = 6000
+    rng = np.random.default_rng(m + seq[0])
+    layers = []
+    for k in seq:
+        cols = [rng.choice(n, size=int(rng.integers(8, k + 1)), replace=False) for _ in range(n)]
+        cols[7] = rng.choice(n, size=k, replace=False)
+        cp, ri, v = csc(rng, n, cols, 0.18)
+        layers.append((cp, ri, v, np.full(n, -0.3, np.float32)))
+    y0 = (rng.random((m, n)) < rng.uniform(0.2, 0.7, size=(m, 1))).astype(np.float32)
+    log(f"rows between tiles {seq} m={m}")
+    gpu, cats = run(n, layers, y0)
+    assert 0 < cats.size
+
+
+def test_rows_to_codes_and_back():
+    """2,500 rows whose layer outputs are many values (rows), then one value (the encoder reads them as tiles
+    and the layer gathers codes), then many again: rows to tiles to codes to rows."""
+    n, m = 6000, 2500
+    rng = np.random.default_rng(3)
+    layers = [layer(rng, n, "random") for _ in range(4)]
+    layers[1] = (*layers[1][:3], np.full(n, 40.0, np.float32))  # every output 32
+    cp, ri, v, b = layers[2]
+    layers[2] = (cp, ri, v * np.float32(0.25), b)  # 32 inputs of 32 sum to 16 on average: not saturated
+    y0 = (rng.random((m, n)) * 2).astype(np.float32)
+    gpu, cats = run(n, layers, y0)
+    from paper_1909_05631_amd import sdnn
+    kinds = [sdnn.KERNEL_KINDS[int(k)] for k in gpu.net.layer_info()[0]]
+    assert kinds == ["k_layer_gfm", "k_layer_gfm", "k_layer_gfm_u8", "k_layer_gfm"]
+    assert cats.size == m
+
+
+def test_two_handles_in_turn():
+    """Two networks of one width on one stream keep their own rows and maps."""
+    n, m = 9000, 600
+    rng = np.random.default_rng(9)
+    nets = []
+    for i in range(2):
+        layers = [layer(rng, n, "random") for _ in range(2)]
+        y0 = rng.random((m, n)).astype(np.float32)
+        gpu = GpuNet(n, 2)
+        for l, (cp, ri, v, b) in enumerate(layers):
+            gpu.load(l, cp, ri, v, b)
+        nets.append((gpu, layers, y0))
+    for gpu, layers, y0 in nets + nets[::-1]:
+        cats = gpu.run(y0)
+        assert_parity(gpu, oracle_run(y0, layers), cats)
