@@ -109,6 +109,13 @@ __device__ __forceinline__ float activate(float z, float b, float ymax) {
 // pins the issue order of software-pipelined loads.
 __device__ __forceinline__ void mem_fence_compiler() { asm volatile("" ::: "memory"); }
 
+// Barrier of a workgroup that orders LDS accesses only: global loads and stores in flight are not waited for.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // Sets bits m in a liveness mask word that many workgroups report to. They report mostly the same
 // rows, and hundreds of atomics on one word from workgroups that finish together serialize (several
 // us per launch), so only bits not yet set go through an atomic. Within a layer bits are only ever
@@ -532,7 +539,7 @@ __global__ __launch_bounds__(1024) void k_layer_lds(const float *__restrict__ yi
       const int2 *ej = ell + j;
       if (ell16) {
         // 32 sources per column, eight per 16-byte load ([4][N][8] u16), with their weights in the
-        // same grouping (w8, two 16-byte loads per eight) or the layer's one weight wc; all loads
+        // grouping of 4 (w8, two 16-byte loads per eight) or the layer's one weight wc; all loads
         // are in flight before the first group's LDS reads
         uint4 ix[4];
         float4 wq[8];
@@ -542,8 +549,8 @@ __global__ __launch_bounds__(1024) void k_layer_lds(const float *__restrict__ yi
           const float4 *w4 = reinterpret_cast<const float4 *>(w8);
 #pragma unroll
           for (int g = 0; g < 4; ++g) {
-            wq[2 * g] = w4[((size_t)g * ncols + j) * 2];
-            wq[2 * g + 1] = w4[((size_t)g * ncols + j) * 2 + 1];
+            wq[2 * g] = w4[(size_t)(2 * g) * ncols + j];
+            wq[2 * g + 1] = w4[(size_t)(2 * g + 1) * ncols + j];
           }
         } else {
 #pragma unroll
@@ -648,11 +655,228 @@ __global__ __launch_bounds__(1024) void k_layer_lds(const float *__restrict__ yi
   }
 }
 
+// A pointer or a number that is the same in every lane, in scalar registers.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+template <class T>
+__device__ __forceinline__ T *uniform(T *p) {
+  const unsigned long long v = reinterpret_cast<unsigned long long>(p);
+  return reinterpret_cast<T *>(((unsigned long long)(unsigned)uniform((int)(v >> 32)) << 32) |
+                               (unsigned)uniform((int)(unsigned)v));
+}
+// p[i] of global memory, the base in scalar registers and a 32-bit offset in a vector one
+template <class T>
+__device__ __forceinline__ T at32(const T *p, unsigned i) {
+  typedef const char __attribute__((address_space(1))) *global_bytes;
+  typedef const T __attribute__((address_space(1))) *global_t;
+  return *(global_t)((global_bytes)p + i * (unsigned)sizeof(T));
+}
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// The rows (bits) of a wave in which any lane's flag is set: lane holds rows 4 (lane % LPO) + c, c < RPL,
+// flag bit c.
+template <int LPO, int RPL>
+__device__ __forceinline__ unsigned wave_rows(unsigned flags) {
+  constexpr unsigned long long kEvery = LPO == 1   ? ~0ull
+                                        : LPO == 2 ? 0x5555555555555555ull
+                                        : LPO == 4 ? 0x1111111111111111ull
+                                                   : 0x0101010101010101ull;
+  unsigned bits = 0u;
+#pragma unroll
+  for (int c = 0; c < RPL; ++c) {
+    const unsigned long long m = __ballot((flags >> c) & 1u);
+#pragma unroll
+    for (int q = 0; q < LPO; ++q) bits |= ((m >> q) & kEvery) != 0ull ? 1u << (RPL * q + c) : 0u;
+  }
+  return bits;
+}
+
+// k_layer_lds for a layer of 32-source lists with per-edge weights and N % 4 == 0 (the default kernels on
+// such layers): same tiles, lanes, sums and placement. The lists of a round are replaced by the next
+// round's (or the next item's first) 8 terms at a time as they are summed, and a wave that has
+// finished an item loads the next one's rows while the others finish, so that neither latency is
+// waited for between the LDS reads.
+// Bound: the LDS reads, 64% of the time (60% of that bank conflicts, see bank_placement). 4096 neurons,
+// 143,000 rows in 4 layers: 2.49 -> 2.21 ms; 1024 neurons, 10 layers of 60,000 rows and fewer: 1.00 ->
+// 0.87 ms. A multiply-add that forms an LDS address in one instruction instead of two changed nothing.
+template <int B>
+__global__ __launch_bounds__(1024) void k_layer_lds32(const float *__restrict__ yin, float *__restrict__ yout, int N,
+                                                      const u32x4 *__restrict__ ell16, const f32x4 *__restrict__ w8,
+                                                      const float *__restrict__ bias, float ymax,
+                                                      const int *__restrict__ ids, const int *__restrict__ count,
+                                                      unsigned *__restrict__ masks, int *__restrict__ rownz,
+                                                      const unsigned short *__restrict__ place) {
+  static_assert(B == 8 || B == 16 || B == 32, "2 to 8 lanes per output");
+  constexpr int LPO = B / 4;    // lanes per output, 4 rows each
+  constexpr int OPW = 64 / LPO; // outputs per wave instruction
+  constexpr int kPerRound = 16 * OPW;
+  constexpr int kAhead = 5;
+  constexpr int kStage = kLdsTileBytes / 64 / 1024;  // 4 x 4 blocks of the tile per thread
+  extern __shared__ float4 smem[];
+  const char *tile = reinterpret_cast<const char *>(smem);
+  float *tilef = reinterpret_cast<float *>(smem);
+  __shared__ unsigned rowlive, rowany;
+  const int R = *count;
+  const int ntiles = (R + B - 1) / B;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int quad = lane % LPO, jl = lane / LPO;
+  const int rounds = (N + kPerRound - 1) / kPerRound;
+  const Chunking ch = chunking(ntiles, rounds);
+  const int items = ntiles * ch.nchunks;
+  if ((int)blockIdx.x >= items) return;  // uniform over the workgroup
+  if (tid == 0) {
+    rowlive = 0u;
+    rowany = 0u;
+  }
+  const int NQ = N >> 2;
+  // this thread's blocks of the tile: rows 4 quad .., neurons 4 q .. with q = (u 1024 + tid) / LPO
+  const int q0 = tid / LPO;
+  unsigned rk[kStage][2];  // their tile rows, two per word
+#pragma unroll
+  for (int u = 0; u < kStage; ++u) {
+    const int q = min(q0 + u * (1024 / LPO), NQ - 1);
+    if (place) {
+      const u32x2 x = at32(reinterpret_cast<const u32x2 *>(place), (unsigned)q);
+      rk[u][0] = x.x;
+      rk[u][1] = x.y;
+    } else {
+      rk[u][0] = (unsigned)(4 * q) | ((unsigned)(4 * q + 1) << 16);
+      rk[u][1] = (unsigned)(4 * q + 2) | ((unsigned)(4 * q + 3) << 16);
+    }
+  }
+  // row ids of this lane's 4 rows of item w (rows past the list: the last row, never stored)
+  auto take_ids = [&](int w, int (&id)[4]) {
+    const int p = w / ch.nchunks * B + quad * 4;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) id[c] = ids[min(p + c, R - 1)];
+  };
+  float4 v[kStage][4];
+  auto load_rows = [&](const int (&id)[4]) {
+#pragma unroll
+    for (int u = 0; u < kStage; ++u) {
+      const int q = min(q0 + u * (1024 / LPO), NQ - 1);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) v[u][c] = reinterpret_cast<const float4 *>(yin + (size_t)id[c] * N)[q];
+    }
+  };
+  u32x4 ix[4];
+  f32x4 wq[8];
+  auto load_group = [&](int g, unsigned at) {
+    ix[g] = at32(ell16, (unsigned)(g * N) + at);
+    wq[2 * g] = at32(w8, (unsigned)(2 * g * N) + at);
+    wq[2 * g + 1] = at32(w8, (unsigned)((2 * g + 1) * N) + at);
+  };
+  // the first position of this lane in item w
+  auto first = [&](int w) { return (w % ch.nchunks) * ch.rounds_per_chunk * kPerRound + wave * OPW + jl; };
+  int id[4], nid[4];
+  take_ids(blockIdx.x, id);
+  load_rows(id);
+  {
+    const unsigned at = (unsigned)min(first(blockIdx.x), N - 1);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) load_group(g, at);
+  }
+  for (int w = blockIdx.x; w < items; w += gridDim.x) {
+    const int t = w / ch.nchunks, c = w % ch.nchunks;
+    const int nvalid = min(B, R - t * B);
+    const bool count_nz = rownz != nullptr && c == 0;
+    // ---- the rows as tile[place[k]][b]
+    unsigned any = 0u;
+#pragma unroll
+    for (int u = 0; u < kStage; ++u) {
+      if (q0 + u * (1024 / LPO) < NQ) {
+        float *dst = tilef + quad * 4;
+        *reinterpret_cast<float4 *>(dst + (rk[u][0] & 0xffffu) * B) = make_float4(v[u][0].x, v[u][1].x, v[u][2].x, v[u][3].x);
+        *reinterpret_cast<float4 *>(dst + (rk[u][0] >> 16) * B) = make_float4(v[u][0].y, v[u][1].y, v[u][2].y, v[u][3].y);
+        *reinterpret_cast<float4 *>(dst + (rk[u][1] & 0xffffu) * B) = make_float4(v[u][0].z, v[u][1].z, v[u][2].z, v[u][3].z);
+        *reinterpret_cast<float4 *>(dst + (rk[u][1] >> 16) * B) = make_float4(v[u][0].w, v[u][1].w, v[u][2].w, v[u][3].w);
+        if (count_nz)
+#pragma unroll
+          for (int b = 0; b < 4; ++b) any |= (any_nonzero(v[u][b]) ? 1u : 0u) << b;
+      }
+    }
+    const int next = min(w + (int)gridDim.x, items - 1);
+    take_ids(next, nid);
+    if (count_nz) {
+      const unsigned rows = wave_rows<LPO, 4>(any);
+      if (lane == 0 && rows) atomicOr(&rowany, rows);
+    }
+    lds_barrier();
+    // ---- lane (quad, jl) owns rows 4 quad .. of output j
+    const char *tq = tile + quad * 16;
+    unsigned lm = 0u;
+    const int r_end = min(rounds, (c + 1) * ch.rounds_per_chunk);
+    int todo = r_end - c * ch.rounds_per_chunk, j = first(w);
+#pragma unroll 1
+    for (; todo > 0; --todo) {
+      asm volatile("" : "+s"(todo));  // (one body for every round)
+      const int jn = todo == 1 ? first(next) : j + kPerRound;
+      const unsigned at = (unsigned)min(jn, N - 1);
+      const float bj = at32(bias, (unsigned)min(j, N - 1));
+      float a[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+      auto rd = [&](int sl) {
+        const unsigned pr = ix[sl / 8][(sl % 8) / 2];
+        return *reinterpret_cast<const float4 *>(tq + ((sl & 1) ? (pr >> 16) : (pr & 0xffffu)) * (unsigned)(B * 4));
+      };
+      float4 buf[kAhead];
+#pragma unroll
+      for (int q = 0; q < kAhead; ++q) buf[q] = rd(q);
+#pragma unroll
+      for (int sl = 0; sl < 32; ++sl) {
+        __builtin_amdgcn_sched_barrier(0);
+        const float ws = wq[sl / 4][sl % 4];
+        const float4 y = buf[sl % kAhead];
+        a[0] = fmaf(y.x, ws, a[0]);
+        a[1] = fmaf(y.y, ws, a[1]);
+        a[2] = fmaf(y.z, ws, a[2]);
+        a[3] = fmaf(y.w, ws, a[3]);
+        if (sl + kAhead < 32) buf[sl % kAhead] = rd(sl + kAhead);
+        if (sl % 8 == 7) {
+          // (summed here, also on lanes past the last column, whose sums are not stored)
+          pin4(a[0], a[1], a[2], a[3]);
+          load_group(sl / 8, at);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (j < N) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          const float y = activate(a[b], bj, ymax);
+          if (quad * 4 + b < nvalid) {
+            yout[(size_t)id[b] * N + j] = y;
+            lm |= (y > 0.0f ? 1u : 0u) << b;
+          }
+        }
+      }
+      j = jn;
+    }
+    // a wave that is done loads the next item's rows while the others finish
+    load_rows(nid);
+    mem_fence_compiler();
+    const unsigned rows = wave_rows<LPO, 4>(lm);
+    if (lane == 0 && rows) atomicOr(&rowlive, rows);
+    lds_barrier();  // every read of the tile is done
+    if (tid < 64) {
+      const unsigned m = rowlive, nz = rowany;
+      if (tid == 0 && m) atomicOr(&masks[t], m);
+      if (count_nz && tid < nvalid && ((nz >> tid) & 1u)) rownz[ids[t * B + tid]] = 1;
+      if (tid == 0) {
+        rowlive = 0u;
+        rowany = 0u;
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < 4; ++b) id[b] = nid[b];
+    lds_barrier();
+  }
+}
+
 // Device view of one layer for kernels that run several layers in one launch.
 struct LayerPtr {
   const int2 *ell;     // slot-major ELL, offsets in units of 1 << ell_shift bytes per source
   const uint4 *ell16;  // layer with 32 sources per column: [4][D][8] u16 sources, else null
-  const float *w8;     // with ell16: the weights in the same grouping, [4][D][8] fp32; null for a
+  const float *w8;     // with ell16: the weights, [8][D][4] fp32 (four per 16-byte load); null for a
                        // uniform layer (weight w)
   const float *bias;
   const int *cols;     // with ell16: the D columns computed (null: all N, D = N)
@@ -748,8 +972,8 @@ __global__ __launch_bounds__(1024) void k_layers_lds(const float *__restrict__ y
           const float4 *w4 = reinterpret_cast<const float4 *>(P.w8);
 #pragma unroll
           for (int g = 0; g < 4; ++g) {
-            wq[2 * g] = w4[((size_t)g * ncols + jp) * 2];
-            wq[2 * g + 1] = w4[((size_t)g * ncols + jp) * 2 + 1];
+            wq[2 * g] = w4[(size_t)(2 * g) * ncols + jp];
+            wq[2 * g + 1] = w4[(size_t)(2 * g + 1) * ncols + jp];
           }
         } else {
 #pragma unroll
@@ -813,6 +1037,158 @@ __global__ __launch_bounds__(1024) void k_layers_lds(const float *__restrict__ y
   if (l == L && lb) {
     // ta holds the output of layer L - 1
     for (int it = tid; it < N * B; it += blockDim.x) {
+      const int b = it / N, k = it % N;
+      if ((lb >> b) & 1u) yout[(size_t)ids[p0 + b] * N + k] = ta[(size_t)k * B + b];
+    }
+    if (tid < B && ((lb >> tid) & 1u)) atomicOr(&masks[(p0 + tid) >> 5], 1u << ((p0 + tid) & 31));
+  }
+}
+
+// k_layers_lds for networks whose every layer has 32-source lists in grouped order with per-edge weights
+// (the default kernels on such layers): same tiles, lanes and sums. The lists do not depend on the rows,
+// so they are loaded a round ahead, also across the end of a layer: the registers of a group of 8
+// terms take the next round's group (or the next layer's) as soon as it has been summed. A layer
+// ends with one barrier, for LDS alone (a full one would wait for the lists too), and the live rows
+// are counted in registers, 64 layers at a time.
+// Bound: the LDS reads (random rows; see conflict_grouped_order) and, for one or two rows, the lists, 6
+// bytes per edge through one CU's L1. Per layer at 1024 neurons: 4.1 -> 2.8 us (one row), 3.7 -> 2.5
+// (two rows per workgroup), 11.7 -> 9.3 (16 rows); at 4096 (two rows) 12.0 -> 11.1.
+template <int B>
+__global__ __launch_bounds__(1024) void k_layers_lds32(const float *__restrict__ yin, float *__restrict__ yout, int N,
+                                                       const LayerPtr *__restrict__ lp, int l0, int L, float ymax,
+                                                       const int *__restrict__ ids, const int *__restrict__ count,
+                                                       int *__restrict__ counts, unsigned *__restrict__ masks) {
+  constexpr int RPL = B < 4 ? B : 4;
+  constexpr int LPO = B / RPL, OPW = 64 / LPO;
+  constexpr int kAhead = 6;  // LDS reads in flight ahead of their fmas
+  extern __shared__ float4 smem[];
+  // live rows of layer l in livebits[l % 3]; a word is cleared one layer before its use, when every
+  // wave is past its last reading
+  __shared__ unsigned livebits[3];
+  float *ta = reinterpret_cast<float *>(smem);
+  float *tc = ta + (size_t)N * B;
+  const int R = *count;
+  const int p0 = blockIdx.x * B;
+  if (p0 >= R) return;  // uniform over the workgroup
+  const int nvalid = min(B, R - p0);
+  const unsigned valid = (1u << nvalid) - 1u;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int quad = lane % LPO, jl = lane / LPO;
+  constexpr int kPerRound = 16 * OPW;
+  const int j0 = wave * OPW + jl;  // this lane's output position in a round
+  const int rounds = (N + kPerRound - 1) / kPerRound;
+  // the lists of the round ahead: sources and weights of 4 groups of 8 terms, and the output column
+  u32x4 ix[4];
+  f32x4 wq[8];
+  int col;
+  const u32x4 *q16 = nullptr;
+  const f32x4 *q8 = nullptr;
+  const int *qcols = nullptr;
+  auto take = [&](int l, const float **bias) {
+    const LayerPtr *q = lp + l;
+    q16 = uniform(reinterpret_cast<const u32x4 *>(q->ell16));
+    q8 = uniform(reinterpret_cast<const f32x4 *>(q->w8));
+    qcols = uniform(q->cols);
+    *bias = uniform(q->bias);
+  };
+  const float *bias = nullptr, *bias_next = nullptr;
+  take(l0, &bias);
+  {
+    const unsigned at = (unsigned)min(j0, N - 1);
+    col = at32(qcols, at);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      ix[g] = at32(q16, (unsigned)(g * N) + at);
+      wq[2 * g] = at32(q8, (unsigned)(2 * g * N) + at);
+      wq[2 * g + 1] = at32(q8, (unsigned)((2 * g + 1) * N) + at);
+    }
+  }
+  // stage the rows as ta[k][b] (reads run along k); positions past the list are zero
+  for (int it = tid; it < N * B; it += 1024) {
+    const int b = it / N, k = it % N;
+    ta[(size_t)k * B + b] = b < nvalid ? yin[(size_t)ids[p0 + b] * N + k] : 0.0f;
+  }
+  if (tid < 3) livebits[tid] = 0u;
+  lds_barrier();
+  unsigned lb = valid;
+  int hist = 0;  // wave 0, lane l % 64: live rows after layer l
+  int l = l0;
+  for (; l < L; ++l) {
+    if (tid == 0) livebits[(l + 1) % 3] = 0u;
+    unsigned lm = 0u;  // this lane's rows with a positive output: bit c is row RPL quad + c
+    const char *tq = reinterpret_cast<const char *>(ta) + quad * (RPL * 4);
+    int todo = rounds, jp = j0;
+#pragma unroll 1
+    for (; todo > 0; --todo) {
+      asm volatile("" : "+s"(todo));  // (one body for every round)
+      const int j = col;
+      const float bj = at32(bias, (unsigned)j);
+      // the round ahead: of this layer, or the first of the next (after the last layer: its own, unused)
+      if (todo == 1) take(min(l + 1, L - 1), &bias_next);
+      const int jn = todo == 1 ? j0 : jp + kPerRound;
+      const unsigned at = (unsigned)min(jn, N - 1);
+      col = at32(qcols, at);
+      float a[RPL];
+#pragma unroll
+      for (int c = 0; c < RPL; ++c) a[c] = 0.0f;
+      auto src_of = [&](int sl) {
+        const unsigned pr = ix[sl / 8][(sl % 8) / 2];
+        return (sl & 1) ? (pr >> 16) : (pr & 0xffffu);
+      };
+      float buf[kAhead][RPL];
+#pragma unroll
+      for (int q = 0; q < kAhead; ++q) lds_rows_load<RPL>(tq + src_of(q) * (unsigned)(B * 4), buf[q]);
+#pragma unroll
+      for (int sl = 0; sl < 32; ++sl) {
+        __builtin_amdgcn_sched_barrier(0);
+        const float w = wq[sl / 4][sl % 4];
+#pragma unroll
+        for (int c = 0; c < RPL; ++c) a[c] = fmaf(buf[sl % kAhead][c], w, a[c]);
+        if (sl + kAhead < 32) lds_rows_load<RPL>(tq + src_of(sl + kAhead) * (unsigned)(B * 4), buf[sl % kAhead]);
+        if (sl % 8 == 7) {
+          // (summed here, also on lanes past the last column, whose sums are not stored)
+#pragma unroll
+          for (int c = 0; c < RPL; ++c) asm volatile("" : "+v"(a[c]));
+          const int g = sl / 8;
+          ix[g] = at32(q16, (unsigned)(g * N) + at);
+          wq[2 * g] = at32(q8, (unsigned)(2 * g * N) + at);
+          wq[2 * g + 1] = at32(q8, (unsigned)((2 * g + 1) * N) + at);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (jp < N) {
+        float y[RPL];
+#pragma unroll
+        for (int c = 0; c < RPL; ++c) {
+          y[c] = activate(a[c], bj, ymax);
+          lm |= (y[c] > 0.0f ? 1u : 0u) << c;
+        }
+        lds_rows_store<RPL>(tc + (size_t)j * B + quad * RPL, y);
+      }
+      jp = jn;
+    }
+    const unsigned bits = wave_rows<LPO, RPL>(lm);
+    if (lane == 0 && bits) atomicOr(&livebits[l % 3], bits);
+    lds_barrier();  // tc is complete, every read of ta is done
+    lb = livebits[l % 3] & valid;
+    if (wave == 0) {
+      if (lane == (l & 63)) hist = __popc(lb);
+      if ((l & 63) == 63) {
+        if (hist) atomicAdd(&counts[l - 63 + lane + 1], hist);
+        hist = 0;
+      }
+    }
+    float *t = ta;
+    ta = tc;
+    tc = t;
+    bias = bias_next;
+    if (!lb) break;
+  }
+  // the layers since the last multiple of 64 (a lane whose layer did not run holds 0)
+  if (wave == 0 && hist) atomicAdd(&counts[(min(l, L - 1) & ~63) + lane + 1], hist);
+  if (l == L && lb) {
+    // ta holds the output of layer L - 1
+    for (int it = tid; it < N * B; it += 1024) {
       const int b = it / N, k = it % N;
       if ((lb >> b) & 1u) yout[(size_t)ids[p0 + b] * N + k] = ta[(size_t)k * B + b];
     }
@@ -1142,13 +1518,6 @@ template <class F, int... I>
 __device__ __forceinline__ void static_for(F &&f, std::integer_sequence<int, I...>) {
   (f(std::integral_constant<int, I>{}), ...);
 }
-// Barrier of a workgroup that orders LDS accesses only: global stores in flight are not waited for.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // 16 times the low (half = 0) or high u16 of u, in one instruction (a word-select on the operand); four
 // holds 4.
 template <int HALF>
@@ -2882,7 +3251,8 @@ struct LayerDev {
   float w = 0.0f, b = 0.0f;
   // layer with K == 32 on widths staged in LDS, and uniform layer 0 of any width: [K/8][N][8] u16
   // source indices, eight per 16-byte load; unless the layer is uniform, its weights in the same
-  // grouping, [K/8][N][8] fp32 (w8)
+  // order, [K/4][N][4] fp32 (w8): 16-byte loads of consecutive columns are consecutive (grouped by 8, each
+  // load touched every second 16 bytes and the fused launch took up to 6% longer)
   const uint4 *ell16 = nullptr;
   const float *w8 = nullptr;
   // LDS row placement for k_layer_lds (path 0, the first kPlacedLayers layers with ell16): neuron k
@@ -3107,6 +3477,7 @@ struct sdnn_net {
   // class (4 << c rows; class 0 also for 1 and 2 rows)
   LayerPtr *lp_dev[3] = {};
   int32_t n_loaded = 0;
+  int32_t n_edge32 = 0;  // layers with grouped 32-source lists and per-edge weights (see k_layers_lds32)
   // last run
   bool ran = false;
   int64_t M = 0;
@@ -3218,6 +3589,9 @@ hipError_t launch_lds(sdnn_net *net, const float *yin, float *yout, const LayerD
   if (!configured) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_layer_lds<B, KC>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, kLdsTileBytes);
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_layer_lds32<B>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, kLdsTileBytes);
     if (e != hipSuccess) return e;
     configured = true;
   }
@@ -3225,6 +3599,13 @@ hipError_t launch_lds(sdnn_net *net, const float *yin, float *yout, const LayerD
   // distinct columns only, when the layer's duplicates need not be computed
   const bool dd = ld.ell16 && ld.ell16c && ld.cols && ld.dedup_ok;
   const bool placed = !dd && ld.place && ld.pell16;
+  if (!dd && ld.ell16 && ld.w8 && !ld.cols && net->N % 4 == 0) {
+    hipLaunchKernelGGL(k_layer_lds32<B>, dim3(net->cus), dim3(1024), lds, net->stream, yin, yout, net->N,
+                       reinterpret_cast<const u32x4 *>(placed ? ld.pell16 : ld.ell16),
+                       reinterpret_cast<const f32x4 *>(ld.w8), ld.bias, net->ymax, ids, count, net->masks, rownz,
+                       placed ? ld.place : nullptr);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL((k_layer_lds<B, KC>), dim3(net->cus * per_cu), dim3(1024), lds, net->stream, yin, yout, net->N,
                      ld.ell, ld.K, dd ? ld.ell16c : (placed ? ld.pell16 : ld.ell16), dd ? nullptr : ld.w8, ld.w,
                      ld.bias, net->ymax, ids, count, net->masks, rownz, dd ? ld.cols : nullptr, dd ? ld.D : net->N,
@@ -3616,6 +3997,9 @@ hipError_t launch_layers_lds_b(sdnn_net *net, const float *yin, float *yout, int
   if (!configured) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_layers_lds<B>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, kLdsTileBytes);
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_layers_lds32<B>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, kLdsTileBytes);
     if (e != hipSuccess) return e;
     configured = true;
   }
@@ -3624,6 +4008,11 @@ hipError_t launch_layers_lds_b(sdnn_net *net, const float *yin, float *yout, int
   const size_t lds = (size_t)2 * net->N * B * sizeof(float);
   const int grid = (int)std::max<int64_t>(1, (rows + B - 1) / B);
   const LayerPtr *lp = net->lp_dev[B >= 16 ? 2 : (B == 8 ? 1 : 0)];  // the table grouped for this height
+  if (net->n_edge32 == net->L) {
+    hipLaunchKernelGGL(k_layers_lds32<B>, dim3(grid), dim3(1024), lds, net->stream, yin, yout, net->N, lp, l0, net->L,
+                       net->ymax, ids, count, net->counts, net->masks);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_layers_lds<B>, dim3(grid), dim3(1024), lds, net->stream, yin, yout, net->N, lp, l0,
                      net->L, net->ymax, ids, count, net->counts, net->masks, shift);
   return hipGetLastError();
@@ -4003,7 +4392,7 @@ sdnn_status sdnn_load_layers(sdnn_net *net, int32_t l0, int32_t nl, const int64_
   {
     // 16-bit source indices in groups of 8 per output ([4][N][8] u16, one 16-byte load per group):
     // every layer with 32 sources per column on widths staged in LDS, with its weights grouped the
-    // same way ([4][N][8] fp32) unless it is uniform; and layer 0 of a uniform network of any width
+    // by four ([8][N][4] fp32) unless it is uniform; and layer 0 of a uniform network of any width
     // (for the counting kernel). Columns with fewer than 32 sources are padded with (source 0,
     // weight +0), a no-op term as in the ELL.
     std::vector<int32_t> sel;
@@ -4026,9 +4415,9 @@ sdnn_status sdnn_load_layers(sdnn_net *net, int32_t l0, int32_t nl, const int64_
         for (int32_t j = 0; j < N; ++j) {
           const int deg = (int)(cp[j + 1] - cp[j]);
           for (int sl = 0; sl < 32; ++sl) {
-            const size_t at = ((size_t)(sl / 8) * N + j) * 8 + sl % 8;
-            dst[at] = sl < deg ? (uint16_t)src_at(sel[(size_t)q], cp[j] + sl) : (uint16_t)0;
-            if (weights) wd[at] = sl < deg ? val[cp[j] + sl] : 0.0f;
+            dst[((size_t)(sl / 8) * N + j) * 8 + sl % 8] =
+                sl < deg ? (uint16_t)src_at(sel[(size_t)q], cp[j] + sl) : (uint16_t)0;
+            if (weights) wd[((size_t)(sl / 4) * N + j) * 4 + sl % 4] = sl < deg ? val[cp[j] + sl] : 0.0f;
           }
         }
       });
@@ -4223,9 +4612,8 @@ sdnn_status sdnn_load_layers(sdnn_net *net, int32_t l0, int32_t nl, const int64_
           const int32_t q = ord[(size_t)p];
           gc[(size_t)p] = pos[(size_t)q];
           for (int sl = 0; sl < 32; ++sl) {
-            const size_t at = ((size_t)(sl / 8) * D + p) * 8 + sl % 8;
-            g16[at] = lists[(size_t)q * 32 + sl];
-            if (weights) g32[at] = wl[(size_t)q * 32 + sl];
+            g16[((size_t)(sl / 8) * D + p) * 8 + sl % 8] = lists[(size_t)q * 32 + sl];
+            if (weights) g32[((size_t)(sl / 4) * D + p) * 4 + sl % 4] = wl[(size_t)q * 32 + sl];
           }
         }
       });
@@ -4307,6 +4695,10 @@ sdnn_status sdnn_load_layers(sdnn_net *net, int32_t l0, int32_t nl, const int64_
       }
       HIP_OR_POISON(net, hipMemcpy(net->lp_dev[c] + t0, hp.data(), hp.size() * sizeof(LayerPtr), hipMemcpyHostToDevice));
     }
+  }
+  for (int32_t i = 0; i < nl; ++i) {
+    const LayerDev &ld = net->layers[(size_t)l0 + i];
+    net->n_edge32 += ld.ell16 && ld.w8 && ld.gell16[0] && ld.gcols[0] && ld.gw8[0] && !ld.cols;
   }
   net->n_loaded += nl;
   g_err.clear();

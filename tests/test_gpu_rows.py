@@ -117,3 +117,34 @@ def test_two_handles_in_turn():
     for gpu, layers, y0 in nets + nets[::-1]:
         cats = gpu.run(y0)
         assert_parity(gpu, oracle_run(y0, layers), cats)
+
+
+def offset_layer(rng, n, bias):
+    """32 sources per column: distinct offsets under two permutations."""
+    off = rng.choice(n, size=32, replace=False)
+    p, q = rng.permutation(n), rng.permutation(n)
+    src = np.sort(p[(q[:, None] + off[None, :]) % n], axis=1).astype(np.int32)
+    v = rng.uniform(0.02, 0.11, size=src.size).astype(np.float32)
+    return np.arange(n + 1, dtype=np.int64) * 32, src.reshape(-1), v, np.full(n, bias, np.float32)
+
+
+@pytest.mark.parametrize("n,m,nl", [
+    (32, 70, 3), (36, 1, 130), (100, 300, 66), (1000, 64, 65), (1024, 9000, 5), (1028, 1100, 64), (1030, 600, 4),
+    (2052, 4500, 4), (4092, 2100, 4), (4096, 260, 70),
+])
+def test_lds_widths_lists(n, m, nl):
+    """Widths staged in LDS with 32 sources per column and per-edge weights (lists loaded a round ahead): rounds
+    that the width does not fill, one row and more, tiles and 4-row groups the rows do not fill,
+    depths around the 64 layers after which the fused launch adds its counts, rows that die early and
+    late."""
+    rng = np.random.default_rng(n + nl)
+    dens = rng.uniform(0.2, 0.9, size=(m, 1))
+    y0 = ((rng.random((m, n)) < dens) * rng.uniform(0.2, 1.0, size=(m, n))).astype(np.float32)
+    if m > 2:
+        y0[1] = 0.0
+    layers = [offset_layer(rng, n, -0.30) for _ in range(min(nl, 8))]
+    layers = [layers[l % len(layers)] for l in range(nl)]
+    if nl > 60:  # every row but the strongest dies at layer 60
+        layers[60] = (*layers[60][:3], np.full(n, -58.0, np.float32))
+    log(f"LDS widths, lists ahead: n={n} m={m} layers={nl}")
+    run(n, layers, y0)
