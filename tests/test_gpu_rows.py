@@ -6,6 +6,7 @@ from __future__ import annotations
 import numpy as np
 import pytest
 
+import oracle
 from tests.gpu_util import GpuNet, assert_parity, log, oracle_run
 
 pytestmark = pytest.mark.gpu
@@ -148,3 +149,30 @@ def test_lds_widths_lists(n, m, nl):
         layers[60] = (*layers[60][:3], np.full(n, -58.0, np.float32))
     log(f"LDS widths, lists ahead: n={n} m={m} layers={nl}")
     run(n, layers, y0)
+
+
+@pytest.mark.parametrize("n,m,scale", [(1024, 300, 1.0), (1024, 1, 1.0), (1000, 5000, 1.0), (6000, 700, 0.9), (6000, 60, 1.0)])
+def test_final_rows_in_any_order(n, m, scale):
+    """Final activations for ids that are unsorted, repeated, dead and alive, the whole list of categories, one
+    run of it and none; categories and counts of more and fewer rows than one read-back word holds.
+    Widths in LDS, rows by position (6000 neurons, 700 rows) and tiles (60 rows)."""
+    rng = np.random.default_rng(n + m)
+    dens = rng.uniform(0.3, 0.9, size=(m, 1)) if m > 1 else np.ones((1, 1))
+    y0 = ((rng.random((m, n)) < dens) * np.float32(scale)).astype(np.float32)
+    layers = [offset_layer(rng, n, -0.9) for _ in range(3)]
+    gpu, cats = run(n, layers, y0)
+    o = oracle_run(y0, layers)
+    assert cats.size
+    alive = np.zeros(m, bool)
+    alive[cats] = True
+    asked = [cats, cats[::-1], cats[:2], cats[1:1 + cats.size // 2], np.repeat(cats[:3], 2), rng.integers(0, m, size=50),
+             np.empty(0, np.int64), np.arange(m)]
+    if cats.size > 3:
+        asked.append(np.r_[cats[0], cats[0], cats[2:cats.size]])
+    for ids in asked:
+        got = gpu.net.final_rows(ids)
+        want = np.zeros((ids.size, n), np.float32)
+        want[alive[ids]] = o.rows(ids[alive[ids]])
+        np.testing.assert_array_equal(got, want)
+    np.testing.assert_array_equal(gpu.net.categories(), cats)
+    np.testing.assert_array_equal(gpu.net.live_counts(), oracle.padded_live_counts(o, 3))
