@@ -1806,25 +1806,30 @@ constexpr int kProgLayerShift = 28, kProgGenShift = 48;
 constexpr unsigned long long kProgCountMask = (1ull << kProgLayerShift) - 1;
 constexpr int kProgressAhead = 6;  // layers the host may enqueue ahead of the last reported one
 
-// Partial liveness words of a few-tile layer: worker workgroup (t, s) of a launch with S slots per
-// tile writes the rows of tile t that stayed live in its chunks to part[t * S + s], a plain store
-// (zero or not). The tile's mask word is the OR of its S slots. Hundreds of workgroups that finish
+// Partial liveness words of a few-tile layer: workgroup g (in XCD order, see few_tile) of a launch of G
+// writes the rows of its tile that stayed live in its chunks to part[g], a plain store (zero or not).
+// The tile's mask word is the OR of its workgroups' words. Hundreds of workgroups that finish
 // together would otherwise serialize on one atomic word (several us per launch).
 constexpr int kPartThreads = 256;
 constexpr int kPartLoads = 16;  // words per thread: kPartThreads x kPartLoads >= any launch's slots
 constexpr int kMaxPartWords = kPartThreads * kPartLoads;
 
-// Mask words m[t] = OR of the partial words of tile t (t < nt, S slots each), from the kPartLoads
+// Tile of workgroup g of G, nt tiles: the workgroups in XCD order (an XCD's follow each other) are divided
+// evenly among the tiles, so that every XCD has its share and gathers from at most two tiles. (Whole
+// XCDs per tile left two of eight idle with 3 tiles: 100 rows at 65536 neurons, 93 us per layer.)
+__device__ __forceinline__ int few_tile(int g, int nt, int G) { return g * nt / G; }
+
+// Mask words m[t] = OR of the partial words of tile t (t < nt), from the kPartLoads of the G
 // words each thread of a kPartThreads workgroup loaded (word tid + kPartThreads k). Every thread of
 // the workgroup calls it; m: nt <= 8 words of LDS, returned after a barrier.
-__device__ void or_partials(const unsigned (&pp)[kPartLoads], int S, int nt, unsigned *m) {
+__device__ void or_partials(const unsigned (&pp)[kPartLoads], int G, int nt, unsigned *m) {
   const int tid = threadIdx.x, lane = tid & 63;
   if (tid < 8) m[tid] = 0u;
   __syncthreads();
   for (int t = 0; t < nt; ++t) {
     unsigned v = 0u;
 #pragma unroll
-    for (int k = 0; k < kPartLoads; ++k) v |= (tid + kPartThreads * k) / S == t ? pp[k] : 0u;
+    for (int k = 0; k < kPartLoads; ++k) v |= few_tile(tid + kPartThreads * k, nt, G) == t ? pp[k] : 0u;
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) v |= __shfl_xor(v, d, 64);
     if (lane == 0 && v) atomicOr(&m[t], v);
@@ -1841,12 +1846,12 @@ __device__ __forceinline__ void load_partials(unsigned (&pp)[kPartLoads], const 
 }
 
 // The mask words of a few-tile layer from its partial words (before a compaction reads them).
-__global__ __launch_bounds__(kPartThreads) void k_finalize_masks(const unsigned *__restrict__ part, int S, int nt,
+__global__ __launch_bounds__(kPartThreads) void k_finalize_masks(const unsigned *__restrict__ part, int G, int nt,
                                                                  unsigned *__restrict__ masks) {
   __shared__ unsigned m[8];
   unsigned pp[kPartLoads];
-  load_partials(pp, part, S * nt);
-  or_partials(pp, S, nt, m);
+  load_partials(pp, part, G);
+  or_partials(pp, G, nt, m);
   if (threadIdx.x < nt) masks[threadIdx.x] = m[threadIdx.x];
 }
 
@@ -1858,9 +1863,8 @@ __global__ __launch_bounds__(kPartThreads) void k_finalize_masks(const unsigned 
 // follows ntiles_h, the host's bound on the tiles, so a lane issues its ELL loads and gathers before
 // it has read the list length, which only masks the liveness bits. live_before is the live count two
 // layers back (final when the launch starts); at zero every input is zero and the layer neither
-// gathers nor stores. Liveness goes to partial words part_out (S = per-XCD workgroups x parts slots
-// per tile). Workgroup 0 turns the previous layer's partial words part_prev (prev_S slots, prev_nt
-// tiles) into its mask words masks_prev, or, with part_prev null, reads those words; then it writes
+// gathers nor stores. Liveness goes to partial words part_out, one per workgroup. Workgroup 0
+// turns the previous layer's partial words part_prev (prev_G of them, prev_nt tiles) into its mask words masks_prev, or, with part_prev null, reads those words; then it writes
 // their live count to count_out (if set) and to the progress word (if set), and clears masks_clear.
 // WM picks the weight layout (kWEll, kWOne, kWEdge; see k_layer_gfm). With cols set (kWOne only),
 // only the ncols columns cols[p] are computed (see k_layer_gfm).
@@ -1870,7 +1874,7 @@ __global__ __launch_bounds__(kPartThreads) void k_layer_gfm_small(
     const unsigned short *__restrict__ src16, const float *__restrict__ w32, float wc,
     const float *__restrict__ bias, float ymax,
     const int *__restrict__ npos, int ntiles_h, unsigned *__restrict__ part_out,
-    const unsigned *__restrict__ part_prev, int prev_S, int prev_nt, unsigned *__restrict__ masks_prev,
+    const unsigned *__restrict__ part_prev, int prev_G, int prev_nt, unsigned *__restrict__ masks_prev,
     unsigned *__restrict__ masks_clear, int *__restrict__ count_out, const int *__restrict__ live_before,
     unsigned long long *__restrict__ progress, unsigned long long progress_tag, const int *__restrict__ cols,
     int ncols) {
@@ -1878,15 +1882,14 @@ __global__ __launch_bounds__(kPartThreads) void k_layer_gfm_small(
   __shared__ unsigned wmask[4];
   __shared__ unsigned pmask[8];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int parts = 8 / ntiles_h;
-  const int xcd = blockIdx.x & 7;
+  const int G = gridDim.x;
+  const int wg = (blockIdx.x & 7) * (G >> 3) + (blockIdx.x >> 3);  // in XCD order
   const int nchunks = (ncols + CH - 1) / CH;
-  const int cpp = (nchunks + parts - 1) / parts;
-  const int t = xcd / parts;
-  const bool worker = xcd < ntiles_h * parts;
-  const int cbeg = (xcd % parts) * cpp, cend = worker ? min(nchunks, cbeg + cpp) : 0;
+  const int t = few_tile(wg, ntiles_h, G);
+  // the tile's workgroups: first, first + 1, ..., taking its chunks in turn
+  const int first = (t * G + ntiles_h - 1) / ntiles_h;
+  const int step = ((t + 1) * G + ntiles_h - 1) / ntiles_h - first;
   const int q = lane & 7, h = lane >> 3;
-  const int per_xcd = gridDim.x >> 3;
   const char *tbase = reinterpret_cast<const char *>(fin + (size_t)t * N * FMR) + q * 16;
   float *obase = fout + (size_t)t * N * FMR + q * 4;
   const bool wg0 = blockIdx.x == 0;
@@ -1898,7 +1901,7 @@ __global__ __launch_bounds__(kPartThreads) void k_layer_gfm_small(
   const int count_before = __hip_atomic_load(live_before + zero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   // workgroup 0: the previous layer's partial words, in flight during its chunk
   unsigned pp[kPartLoads];
-  if (wg0 && part_prev) load_partials(pp, part_prev, prev_S * prev_nt);
+  if (wg0 && part_prev) load_partials(pp, part_prev, prev_G);
   int R = 0;           // list length
   unsigned pm = 0u;    // lane i < ntiles_h of workgroup 0: the previous layer's mask word of tile i
   unsigned lm = 0u;
@@ -1962,16 +1965,16 @@ __global__ __launch_bounds__(kPartThreads) void k_layer_gfm_small(
     // positions past the list length (up to the host's tile bound) are stored too: nothing reads them
     if (j < ncols && !dead) store_stream(reinterpret_cast<float4 *>(obase + (size_t)col * FMR), y);
   };
-  int chunk = cbeg + (int)(blockIdx.x >> 3);
-  if (chunk < cend) {
+  int chunk = wg - first;
+  if (chunk < nchunks) {
     run_chunk(chunk, std::true_type{});
-    for (chunk += per_xcd; chunk < cend; chunk += per_xcd) run_chunk(chunk, std::false_type{});
+    for (chunk += step; chunk < nchunks; chunk += step) run_chunk(chunk, std::false_type{});
   }
   if (wg0) {
     // (workgroup 0 always runs chunk 0, so R is loaded)
     const int ntiles = min(8, (R + FMR - 1) / FMR);
     if (part_prev) {
-      or_partials(pp, prev_S, prev_nt, pmask);
+      or_partials(pp, prev_G, prev_nt, pmask);
       if (tid < prev_nt) masks_prev[tid] = pmask[tid];
       pm = lane < prev_nt ? pmask[lane] : 0u;
     }
@@ -1990,12 +1993,10 @@ __global__ __launch_bounds__(kPartThreads) void k_layer_gfm_small(
   for (int d = 32; d >= 1; d >>= 1) lm |= __shfl_xor(lm, d, 64);
   if (lane == 0) wmask[wave] = lm;
   __syncthreads();
-  if (tid == 0 && worker) {
+  if (tid == 0) {
     const int nvalid = min(FMR, R - t * FMR);
     const unsigned valid = nvalid >= 32 ? 0xffffffffu : (nvalid > 0 ? (1u << nvalid) - 1u : 0u);
-    const int S = per_xcd * parts;
-    part_out[t * S + (blockIdx.x >> 3) * parts + xcd % parts] =
-        count_before == 0 ? 0u : (wmask[0] | wmask[1] | wmask[2] | wmask[3]) & valid;
+    part_out[wg] = count_before == 0 ? 0u : (wmask[0] | wmask[1] | wmask[2] | wmask[3]) & valid;
   }
 }
 
@@ -3661,35 +3662,34 @@ hipError_t launch_lds_k(sdnn_net *net, const float *yin, float *yout, const Laye
 }
 
 // A layer of at most 8 tiles with K == 32 (see k_layer_gfm_small). Liveness goes to the partial
-// words part_out; *S_out and *nt_out receive their slots per tile and tiles.
+// words part_out; *G_out and *nt_out receive their number and the tiles.
 hipError_t launch_gfm_small(sdnn_net *net, const LayerDev &ld, const float *fin, float *fout, const int *npos,
-                            int64_t max_tiles, unsigned *part_out, const unsigned *part_prev, int prev_S, int prev_nt,
+                            int64_t max_tiles, unsigned *part_out, const unsigned *part_prev, int prev_G, int prev_nt,
                             unsigned *masks_prev, unsigned *masks_clear, int *count_out, const int *live_before,
-                            unsigned long long *progress, unsigned long long progress_tag, int *S_out, int *nt_out) {
+                            unsigned long long *progress, unsigned long long progress_tag, int *G_out, int *nt_out) {
   const bool dd = ld.src16 && ld.cols && ld.dedup_ok;  // distinct columns only
   const int ncols = dd ? ld.D : net->N;
   const int nchunks = (ncols + 31) / 32;
   const int ntiles_h = (int)std::max<int64_t>(1, std::min<int64_t>(8, max_tiles));
-  const int parts = 8 / ntiles_h;
-  // at most kMaxPartWords / 8 workgroups per XCD, so that the partial words fit their buffer
-  const int per_xcd = std::max(1, std::min({kMaxPartWords / 8, 2 * net->cus, (nchunks + parts - 1) / parts}));
+  // at most kMaxPartWords workgroups, so that the partial words fit their buffer
+  const int per_xcd = std::max(1, std::min({kMaxPartWords / 8, 2 * net->cus, (ntiles_h * nchunks + 7) / 8}));
   const dim3 grid(8 * per_xcd);
-  *S_out = per_xcd * parts;
+  *G_out = 8 * per_xcd;
   *nt_out = ntiles_h;
   if (ld.uniform && ld.src16)
     hipLaunchKernelGGL((k_layer_gfm_small<32, kWOne>), grid, dim3(kPartThreads), 0, net->stream, fin, fout, net->N,
                        ld.ell, dd ? ld.src16c : ld.src16, (const float *)nullptr, ld.w, ld.bias, net->ymax, npos,
-                       ntiles_h, part_out, part_prev, prev_S, prev_nt, masks_prev, masks_clear, count_out, live_before,
+                       ntiles_h, part_out, part_prev, prev_G, prev_nt, masks_prev, masks_clear, count_out, live_before,
                        progress, progress_tag, dd ? ld.cols : nullptr, ncols);
   else if (ld.src16 && ld.w32)
     hipLaunchKernelGGL((k_layer_gfm_small<32, kWEdge>), grid, dim3(kPartThreads), 0, net->stream, fin, fout, net->N,
-                       ld.ell, ld.src16, ld.w32, ld.w, ld.bias, net->ymax, npos, ntiles_h, part_out, part_prev, prev_S,
+                       ld.ell, ld.src16, ld.w32, ld.w, ld.bias, net->ymax, npos, ntiles_h, part_out, part_prev, prev_G,
                        prev_nt, masks_prev, masks_clear, count_out, live_before, progress, progress_tag,
                        (const int *)nullptr, net->N);
   else
     hipLaunchKernelGGL((k_layer_gfm_small<32, kWEll>), grid, dim3(kPartThreads), 0, net->stream, fin, fout, net->N,
                        ld.ell, ld.src16, (const float *)nullptr, ld.w, ld.bias, net->ymax, npos, ntiles_h, part_out,
-                       part_prev, prev_S, prev_nt, masks_prev, masks_clear, count_out, live_before, progress,
+                       part_prev, prev_G, prev_nt, masks_prev, masks_clear, count_out, live_before, progress,
                        progress_tag, (const int *)nullptr, net->N);
   return hipGetLastError();
 }
@@ -4961,11 +4961,11 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
   // mask words, any other reader of the masks needs k_finalize_masks first
   bool parts_pending = false;
   int32_t part_layer = -1;
-  int part_S = 0, part_nt = 0;
+  int part_G = 0, part_nt = 0;
   auto finalize_parts = [&]() -> hipError_t {
     if (!parts_pending) return hipSuccess;
     parts_pending = false;
-    hipLaunchKernelGGL(k_finalize_masks, dim3(1), dim3(kPartThreads), 0, s, net->part[part_layer & 1], part_S, part_nt,
+    hipLaunchKernelGGL(k_finalize_masks, dim3(1), dim3(kPartThreads), 0, s, net->part[part_layer & 1], part_G, part_nt,
                        masks_for(part_layer));
     return hipGetLastError();
   };
@@ -5160,16 +5160,16 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
       int *cnt = compacted ? nullptr : net->counts + l;
       if (small && ld.K == 32) {
         const unsigned *prev = cnt && parts_pending ? net->part[part_layer & 1] : nullptr;
-        int S = 0, nt = 0;
+        int G = 0, nt = 0;
         const unsigned long long tag = (gen << kProgGenShift) | ((unsigned long long)l << kProgLayerShift);
-        HIP_OR_POISON(net, launch_gfm_small(net, ld, fin, fout, npos + cur, tiles(P), net->part[l & 1], prev, part_S,
+        HIP_OR_POISON(net, launch_gfm_small(net, ld, fin, fout, npos + cur, tiles(P), net->part[l & 1], prev, part_G,
                                             part_nt, masks_for(l - 1), masks_for(l + 1), cnt, net->counts + (l - 1),
-                                            follow ? net->progress_dev : nullptr, tag, &S, &nt));
+                                            follow ? net->progress_dev : nullptr, tag, &G, &nt));
         reported = follow;
         fout_cols = ocols_on ? lcur.cols : nullptr;
         parts_pending = true;
         part_layer = l;
-        part_S = S;
+        part_G = G;
         part_nt = nt;
         net->layer_kernel[(size_t)l] = SDNN_KERNEL_GLOBAL_TILE_FEW_ROWS;
         net->layer_launches[(size_t)l] = 1;
