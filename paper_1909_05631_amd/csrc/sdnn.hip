@@ -203,8 +203,10 @@ __device__ __forceinline__ void dict_init(unsigned *dict, int t, int nt) {
     dict[i] = i < KEY ? 0u : i < CODE ? (i == KEY ? 0u : kDictEmpty) : i < NEXT ? (i == CODE ? 0u : kNoCode) : 1u;
 }
 
+// misc[kPaceSlot + x]: layer that workgroup x < 8 of a fused launch runs (see fetch_lists).
 constexpr int kOverflowSlot = 2;
 constexpr int kNposSlot = 4;
+constexpr int kPaceSlot = 8, kMiscWords = 16;
 __global__ void k_init(int *__restrict__ ids, unsigned *__restrict__ masks, unsigned *__restrict__ masks2,
                        unsigned *__restrict__ masks3, int *__restrict__ rownz, int *__restrict__ counts,
                        int *__restrict__ misc, unsigned *__restrict__ dict, int M, int L,
@@ -213,7 +215,7 @@ __global__ void k_init(int *__restrict__ ids, unsigned *__restrict__ masks, unsi
   // value dictionary (see dict_code): code 0 is +0.0, whose key 0 sits in its hash slot 0; every
   // other slot is free and the next code is 1
   if (blockIdx.x == 0) dict_init(dict, threadIdx.x, blockDim.x);
-  if (blockIdx.x == 0 && threadIdx.x < 8) misc[threadIdx.x] = (threadIdx.x == kNposSlot) ? M : 0;
+  if (blockIdx.x == 0 && threadIdx.x < kMiscWords) misc[threadIdx.x] = (threadIdx.x == kNposSlot) ? M : 0;
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < M; i += st) {
     ids[i] = i;
     masks[i] = 0u;
@@ -1089,6 +1091,53 @@ __global__ __launch_bounds__(1024) void k_layers_lds(const float *__restrict__ y
   }
 }
 
+// The helper of a fused launch that leaves CUs idle: on the XCD of worker x < 8 a workgroup loads one word of
+// each 128-byte line of the layers' lists, at most kFetchAhead layers ahead of that worker, so that the
+// XCD's workers find them in its L2 (which holds about 20 layers of 1024 neurons). Every wait ends: the
+// worker stores kPaceDone when it ends, and after kFetchPolls polls the helper gives up.
+// One layer of 1024 neurons for one row takes 1.84 us with its lists in the L2 and 2.3 from beyond it;
+// 120 layers, with the final row, 336 -> 280 us a pass; 64 rows x 30 layers of 1000 134 -> 124. Two and
+// four helpers per XCD were slower (293 us).
+constexpr int kFetchAhead = 12, kPaceEvery = 4, kPaceDone = 0x7fffffff, kFetchPolls = 1 << 14;
+__device__ void fetch_lists(const LayerPtr *__restrict__ lp, int l0, int L, int N, const int *__restrict__ pace) {
+  __shared__ int at;
+  int reached = l0;
+  for (int l = l0 + 1; l < L; ++l) {
+    if (l > reached + kFetchAhead) {
+      if (threadIdx.x == 0) {
+        int v = 0;
+        for (int i = 0; i < kFetchPolls; ++i) {
+          v = __hip_atomic_load(pace, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (l <= v || l - v <= kFetchAhead) break;
+          __builtin_amdgcn_s_sleep(8);
+          if (i == kFetchPolls - 1) v = kPaceDone;
+        }
+        at = v;
+      }
+      __syncthreads();
+      reached = at;
+      __syncthreads();
+      if (reached == kPaceDone) return;  // uniform
+    }
+    // lines of 128 bytes: the sources (64 bytes per column), the weights (128), columns and biases (4 each)
+    const int n1 = (N + 1) / 2, n2 = n1 + N, n3 = n2 + (N + 31) / 32, n4 = n3 + (N + 31) / 32;
+    for (int i = threadIdx.x; i < n4; i += 1024) {
+      const LayerPtr *q = lp + l;
+      const int *a;
+      if (i < n1)
+        a = reinterpret_cast<const int *>(q->ell16) + (size_t)i * 32;
+      else if (i < n2)
+        a = reinterpret_cast<const int *>(q->w8) + (size_t)(i - n1) * 32;
+      else if (i < n3)
+        a = q->cols + (i - n2) * 32;
+      else
+        a = reinterpret_cast<const int *>(q->bias) + (i - n3) * 32;
+      const int v = *a;
+      asm volatile("" : : "v"(v));
+    }
+  }
+}
+
 // k_layers_lds for networks whose every layer has 32-source lists in grouped order with per-edge weights
 // (the default kernels on such layers): same tiles, lanes and sums. The lists do not depend on the rows,
 // so they are loaded a round ahead, also across the end of a layer: the registers of a group of 8
@@ -1103,7 +1152,7 @@ __global__ __launch_bounds__(1024) void k_layers_lds32(const float *__restrict__
                                                        const LayerPtr *__restrict__ lp, int l0, int L, float ymax,
                                                        const int *__restrict__ ids, const int *__restrict__ count,
                                                        int *__restrict__ counts, unsigned *__restrict__ masks,
-                                                       int *__restrict__ rownz) {
+                                                       int *__restrict__ rownz, int *__restrict__ pace, int workers) {
   constexpr int RPL = B < 4 ? B : 4;
   constexpr int LPO = B / RPL, OPW = 64 / LPO;
   constexpr int kAhead = 6;  // LDS reads in flight ahead of their fmas
@@ -1115,7 +1164,14 @@ __global__ __launch_bounds__(1024) void k_layers_lds32(const float *__restrict__
   float *tc = ta + (size_t)N * B;
   const int R = *count;
   const int p0 = blockIdx.x * B;
+  if ((int)blockIdx.x >= workers) {
+    // (workers is a multiple of 8: helper and worker x are on one XCD)
+    const int x = (int)blockIdx.x & 7;
+    if (x * B < R) fetch_lists(lp, l0, L, N, pace + x);
+    return;
+  }
   if (p0 >= R) return;  // uniform over the workgroup
+  const bool paces = pace != nullptr && blockIdx.x < 8;
   const int nvalid = min(B, R - p0);
   const unsigned valid = (1u << nvalid) - 1u;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1164,6 +1220,8 @@ __global__ __launch_bounds__(1024) void k_layers_lds32(const float *__restrict__
   int l = l0;
   for (; l < L; ++l) {
     if (tid == 0) livebits[(l + 1) % 3] = 0u;
+    if (paces && tid == 0 && l % kPaceEvery == 0)
+      __hip_atomic_store(pace + blockIdx.x, l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     unsigned lm = 0u;  // this lane's rows with a positive output: bit c is row RPL quad + c
     const char *tq = reinterpret_cast<const char *>(ta) + quad * (RPL * 4);
     int todo = rounds, jp = j0;
@@ -1233,6 +1291,7 @@ __global__ __launch_bounds__(1024) void k_layers_lds32(const float *__restrict__
     bias = bias_next;
     if (!lb) break;
   }
+  if (paces && tid == 0) __hip_atomic_store(pace + blockIdx.x, kPaceDone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   // the layers since the last multiple of 64 (a lane whose layer did not run holds 0)
   if (wave == 0 && hist) atomicAdd(&counts[(min(l, L - 1) & ~63) + lane + 1], hist);
   if (l == L && lb) {
@@ -4070,8 +4129,14 @@ hipError_t launch_layers_lds_b(sdnn_net *net, const float *yin, float *yout, int
   const int grid = (int)std::max<int64_t>(1, (rows + B - 1) / B);
   const LayerPtr *lp = net->lp_dev[B >= 16 ? 2 : (B == 8 ? 1 : 0)];  // the table grouped for this height
   if (net->n_edge32 == net->L) {
-    hipLaunchKernelGGL(k_layers_lds32<B>, dim3(grid), dim3(1024), lds, net->stream, yin, yout, net->N, lp, l0, net->L,
-                       net->ymax, ids, count, net->counts, net->masks, rownz);
+    // idle CUs fetch the lists ahead, where kFetchAhead layers (200 bytes per neuron) leave room in the L2
+    // (4 MiB) and more layers than that follow
+    const int workers = (grid + 7) / 8 * 8;
+    const bool fetch = workers + 8 <= net->cus && (size_t)net->N * 200 * kFetchAhead <= (size_t)5 << 19 &&
+                       net->L - l0 > kFetchAhead;
+    hipLaunchKernelGGL(k_layers_lds32<B>, dim3(fetch ? workers + 8 : grid), dim3(1024), lds, net->stream, yin, yout,
+                       net->N, lp, l0, net->L, net->ymax, ids, count, net->counts, net->masks, rownz,
+                       fetch ? net->misc + kPaceSlot : nullptr, fetch ? workers : grid);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(k_layers_lds<B>, dim3(grid), dim3(1024), lds, net->stream, yin, yout, net->N, lp, l0,

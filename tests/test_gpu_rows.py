@@ -131,13 +131,14 @@ def offset_layer(rng, n, bias):
 
 @pytest.mark.parametrize("n,m,nl", [
     (32, 70, 3), (36, 1, 130), (100, 300, 66), (1000, 64, 65), (1024, 9000, 5), (1028, 1100, 64), (1030, 600, 4),
-    (2052, 4500, 4), (4092, 2100, 4), (4096, 260, 70),
+    (2052, 4500, 4), (4092, 2100, 4), (4096, 260, 70), (1024, 5, 13), (1024, 5, 14), (1092, 470, 20), (1092, 498, 20),
+    (1096, 3, 20),
 ])
 def test_lds_widths_lists(n, m, nl):
     """Widths staged in LDS with 32 sources per column and per-edge weights (lists loaded a round ahead): rounds
     that the width does not fill, one row and more, tiles and 4-row groups the rows do not fill,
     depths around the 64 layers after which the fused launch adds its counts, rows that die early and
-    late."""
+    late; depths, widths and batches on both sides of the rule for workgroups that fetch lists ahead."""
     rng = np.random.default_rng(n + nl)
     dens = rng.uniform(0.2, 0.9, size=(m, 1))
     y0 = ((rng.random((m, n)) < dens) * rng.uniform(0.2, 1.0, size=(m, n))).astype(np.float32)
