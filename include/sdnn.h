@@ -151,7 +151,8 @@ sdnn_status sdnn_layer_times(sdnn_net *net, double *ms, int64_t *runs);
 typedef enum {
   SDNN_KERNEL_NONE = 0,                 /* layer not run (every row had died) */
   SDNN_KERNEL_LDS_TILE = 1,             /* activation tiles staged in LDS (k_layer_lds) */
-  SDNN_KERNEL_GLOBAL_TILE = 2,          /* fp32 feature-major tiles in global memory (k_layer_gfm) */
+  SDNN_KERNEL_GLOBAL_TILE = 2,          /* fp32 activations in global memory: feature-major tiles (k_layer_gfm) or,
+                                           up to 16384 neurons, rows (k_layer_seg) */
   SDNN_KERNEL_GLOBAL_TILE_CODES = 3,    /* one-byte dictionary codes of the inputs (k_layer_gfm_u8) */
   SDNN_KERNEL_GLOBAL_TILE_FEW_ROWS = 4, /* at most 8 tiles, whole chains in flight (k_layer_gfm_small) */
   SDNN_KERNEL_BITS = 5,                 /* layer 0 from bit-packed binary inputs (k_pack_bits, k_layer_bits) */
