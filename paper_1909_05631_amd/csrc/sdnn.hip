@@ -1613,10 +1613,7 @@ constexpr int kSegThreads = 1024;
 constexpr int kSegOutputs = 16;                // outputs per thread
 constexpr int kSegMaxNeurons = kSegThreads * kSegOutputs;
 constexpr int kSegCap = 10112;                 // sources in LDS: 158 KiB
-#ifndef SDNN_SEG_AHEAD
-#define SDNN_SEG_AHEAD 5
-#endif
-constexpr int kSegAhead = SDNN_SEG_AHEAD;      // LDS reads in flight ahead of the fmas
+constexpr int kSegAhead = 5;                   // LDS reads in flight ahead of the fmas
 constexpr unsigned kNoColumn = 0x80000000u;
 constexpr int kSegGroupWords = 192;            // uint4 words of a group
 static_assert(2 * kSegCap >= kSegMaxNeurons && kSegCap * 16 + 1024 <= 160 * 1024, "two segments cover the widest layer");
