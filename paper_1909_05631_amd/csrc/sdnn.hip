@@ -417,8 +417,8 @@ __global__ __launch_bounds__(256) void k_gather_rows(const float *__restrict__ f
   }
 }
 
-// What the host reads after a run, in coherent host memory that the device writes: the categories' number
-// and (up to kHostIds) ids, and, on request, the live counts (networks of fewer than kHostCounts
+// What the host reads after a run, in coherent host memory that the device writes when the host asks: the
+// categories' number and (up to kHostIds) ids, the live counts (networks of fewer than kHostCounts
 // layers) and the number of nonzero input rows. Reading them costs no copies; each small one from
 // device memory takes about 10 us.
 constexpr int kHostIds = 4096, kHostCounts = 4096;
@@ -428,9 +428,10 @@ struct HostOut {
   int count, nonzero;
 };
 
-__global__ void k_final_ids(const int *__restrict__ ids, const int *__restrict__ count, long long *__restrict__ out,
+// M: rows of the run (the bound holds whatever a caller has done to the workspace since).
+__global__ void k_final_ids(const int *__restrict__ ids, const int *__restrict__ count, int M, long long *__restrict__ out,
                             HostOut *__restrict__ host) {
-  const int R = *count;
+  const int R = max(0, min(*count, M));
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < R; i += gridDim.x * blockDim.x) {
     out[i] = ids[i];
     if (R <= kHostIds) __hip_atomic_store(&host->ids[i], (long long)ids[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -3645,7 +3646,7 @@ struct sdnn_net {
   unsigned long long *notify = nullptr, *notify_dev = nullptr;
   uint32_t notify_seq = 0;
   HostOut *host_out = nullptr, *host_out_dev = nullptr;  // see HostOut
-  bool finished = false;     // the stream has been waited for since the last infer
+  bool finished = false;     // host_out holds the last infer's categories (see finish)
   uint32_t run_gen = 0;      // generation of the current infer, in the progress word's top bits
   std::vector<hipEvent_t> events;
   // profiling
@@ -5562,9 +5563,6 @@ sdnn_status infer_impl(sdnn_net *net, const float *y0, int64_t n_rows, void *wor
   net->layer_launches.assign((size_t)net->L, 0);
   st = net->path == 0 ? infer_lds(net, y0, M) : infer_gfm(net, y0, M);
   if (st != SDNN_OK) return st;
-  hipLaunchKernelGGL(k_final_ids, dim3(std::max(1, std::min(net->cus, (M + 255) / 256 + 1))), dim3(256), 0, s,
-                     net->ids[net->final_list], net->counts + net->layers_run, net->final_ids, net->host_out_dev);
-  HIP_OR_POISON(net, hipGetLastError());
   net->ran = true;
   net->pending_times = net->profiling;
   g_err.clear();
@@ -5575,10 +5573,31 @@ sdnn_status infer_impl(sdnn_net *net, const float *y0, int64_t n_rows, void *wor
 
 namespace {
 
-// Wait for the last infer (once).
+// The handle's device as the current one while kernels are launched on its stream (the caller may have
+// changed it since sdnn_infer).
+struct DeviceGuard {
+  int before = -1;
+  hipError_t status;
+  explicit DeviceGuard(int device) {
+    status = hipGetDevice(&before);
+    if (status != hipSuccess || before == device) before = -1;
+    else status = hipSetDevice(device);
+  }
+  ~DeviceGuard() {
+    if (before >= 0) (void)hipSetDevice(before);
+  }
+};
+
+// The last infer's number of categories and their ids to the host, and wait for them (once). The host's
+// words are the handle's, so only a kernel that the host waits for at once may write them: as the last
+// kernel of sdnn_infer, one still queued on another stream would overwrite a later run's answer.
 hipError_t finish(sdnn_net *net) {
   if (net->finished) return hipSuccess;
-  const hipError_t e = hipStreamSynchronize(net->stream);
+  const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(net->cus, (net->M + 255) / 256 + 1));
+  hipLaunchKernelGGL(k_final_ids, dim3(grid), dim3(256), 0, net->stream, net->ids[net->final_list],
+                     net->counts + net->layers_run, (int)net->M, net->final_ids, net->host_out_dev);
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess) e = hipStreamSynchronize(net->stream);
   net->finished = e == hipSuccess;
   return e;
 }
@@ -5598,6 +5617,8 @@ sdnn_status sdnn_categories(sdnn_net *net, int64_t *ids, int64_t capacity, int64
   if (st != SDNN_OK) return st;
   if (!net->ran) return fail(SDNN_ESTATE, "no inference has run");
   if (!count) return fail(SDNN_EINVAL, "count is null");
+  const DeviceGuard dev(net->device);
+  HIP_OR_POISON(net, dev.status);
   HIP_OR_POISON(net, finish(net));
   if (net->pending_times) {
     for (int32_t l = 0; l < net->layers_run; ++l) {
@@ -5622,18 +5643,19 @@ sdnn_status sdnn_live_counts(sdnn_net *net, int64_t *counts) {
   if (st != SDNN_OK) return st;
   if (!net->ran) return fail(SDNN_ESTATE, "no inference has run");
   if (!counts) return fail(SDNN_EINVAL, "counts is null");
+  const DeviceGuard dev(net->device);
+  HIP_OR_POISON(net, dev.status);
   if (net->L < kHostCounts) {
     hipLaunchKernelGGL(k_host_counts, dim3(1), dim3(1024), 0, net->stream, net->counts, net->L, net->rownz, (int)net->M,
                        net->host_out_dev);
     HIP_OR_POISON(net, hipGetLastError());
     HIP_OR_POISON(net, hipStreamSynchronize(net->stream));
-    net->finished = true;
     counts[0] = net->host_out->nonzero;
     for (int32_t l = 1; l <= net->L; ++l) counts[l] = net->host_out->counts[l];
     g_err.clear();
     return SDNN_OK;
   }
-  HIP_OR_POISON(net, finish(net));
+  HIP_OR_POISON(net, hipStreamSynchronize(net->stream));
   std::vector<int32_t> c((size_t)net->L + 1);
   HIP_OR_POISON(net, hipMemcpy(c.data(), net->counts, c.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
   std::vector<int32_t> nz((size_t)std::max<int64_t>(net->M, 1));
@@ -5653,6 +5675,8 @@ sdnn_status sdnn_final_rows(sdnn_net *net, const int64_t *ids, int64_t n, float 
   if (n < 0 || (n > 0 && (!ids || !out_host))) return fail(SDNN_EINVAL, "bad arguments");
   for (int64_t q = 0; q < n; ++q)
     if (ids[q] < 0 || ids[q] >= net->M) return fail(SDNN_EINVAL, "row id %lld out of range", (long long)ids[q]);
+  const DeviceGuard dev(net->device);
+  HIP_OR_POISON(net, dev.status);
   HIP_OR_POISON(net, finish(net));
   const int32_t c = net->host_out->count;
   std::vector<int64_t> live((size_t)std::max(c, 1));
