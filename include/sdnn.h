@@ -99,7 +99,8 @@ size_t sdnn_workspace_bytes(const sdnn_net *net, int64_t n_rows);
  *   workspace: device pointer, >= sdnn_workspace_bytes(net, n_rows) bytes, 256-byte aligned; owned
  *              by the caller, overwritten, must stay untouched until sdnn_categories returns and
  *              while diagnostics are read.
- *   hip_stream: hipStream_t (NULL = default stream) on which all work is enqueued.
+ *   hip_stream: hipStream_t (NULL = default stream) on which all work is enqueued; not one that is
+ *              being captured into a graph (SDNN_ESTATE for n_rows > 0, nothing is enqueued).
  * Rows that become all zero are dropped from later layers: their activations stay zero for every W
  * and b, since Z = 0 gets no bias. The call enqueues layers in chunks and reads the live-row count
  * back from the device every few layers, so it may block until earlier layers finish; once no row
@@ -107,8 +108,8 @@ size_t sdnn_workspace_bytes(const sdnn_net *net, int64_t n_rows);
 sdnn_status sdnn_infer(sdnn_net *net, const float *y0, int64_t n_rows, void *workspace,
                        size_t workspace_bytes, void *hip_stream);
 
-/* TIMED. sdnn_infer for callers that cannot allocate device memory (code under HIP graph
- * capture, tight serving loops, harnesses that forbid allocation): the same computation and results,
+/* TIMED. sdnn_infer for callers that cannot allocate device memory (tight serving
+ * loops, harnesses that forbid allocation): the same computation and results,
  * with the workspace taken from a 64 MiB array in the library's device memory instead of a caller
  * buffer. Allocates nothing (no hipMalloc, hipFree or allocating library call). The array is one per
  * device, shared by every handle and call on that device, and keeps the last call's contents: calls

@@ -5526,6 +5526,13 @@ sdnn_status infer_impl(sdnn_net *net, const float *y0, int64_t n_rows, void *wor
   int dev = -1;
   HIP_OR_POISON(net, hipGetDevice(&dev));
   if (dev != net->device) return fail(SDNN_EINVAL, "current device %d differs from the handle's device %d", dev, net->device);
+  if (n_rows > 0 && hip_stream) {
+    // a replay could run on any stream, and sdnn_categories waits for this one once (the kernels that wait
+    // for reports cannot be captured at all; the default stream never is)
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(reinterpret_cast<hipStream_t>(hip_stream), &cap) != hipSuccess) (void)hipGetLastError();
+    else if (cap != hipStreamCaptureStatusNone) return fail(SDNN_ESTATE, "the stream is being captured");
+  }
   char *ws = static_cast<char *>(workspace);
   net->M = n_rows;
   ++net->run_gen;

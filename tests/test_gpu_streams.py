@@ -1,10 +1,12 @@
-"""Runs of one handle on streams: the answers are those of the last run whatever else is still queued."""
+"""Runs of one handle on streams: the answers are those of the last run whatever else is still queued, and
+a stream that is being captured is refused."""
 from __future__ import annotations
 
 import numpy as np
 import pytest
 
 import oracle
+from paper_1909_05631_amd import sdnn
 from tests.gpu_util import GpuNet, log, oracle_run, torch_cuda
 
 pytestmark = pytest.mark.gpu
@@ -55,3 +57,20 @@ def test_earlier_run_queued_on_another_stream():
     np.testing.assert_array_equal(cats, o.categories())
     np.testing.assert_array_equal(gpu.net.live_counts(), oracle.padded_live_counts(o, gpu.n_layers))
     np.testing.assert_array_equal(gpu.net.final_rows(cats), o.rows(cats))
+
+
+def test_captured_stream_is_refused():
+    """Categories are read after a wait for the handle's stream, which a replay need not run on: a capturing
+    stream is refused before anything is enqueued, and the handle goes on working."""
+    torch = torch_cuda()
+    gpu, layers = small_net()
+    y = inputs(np.random.default_rng(6), 12, gpu.n, [3])
+    yd = torch.from_numpy(y).cuda()
+    torch.cuda.synchronize()
+    log("captured stream")
+    with torch.cuda.graph(torch.cuda.CUDAGraph()):
+        with pytest.raises(sdnn.SdnnError) as e:
+            gpu.net.infer_static(yd, 12, torch.cuda.current_stream())
+    assert e.value.name == "SDNN_ESTATE"
+    gpu.net.infer_static(yd, 12, torch.cuda.current_stream())
+    np.testing.assert_array_equal(gpu.net.categories(), oracle_run(y, layers).categories())
