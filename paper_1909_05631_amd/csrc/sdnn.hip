@@ -825,6 +825,7 @@ __global__ __launch_bounds__(1024) void k_layer_lds32(const float *__restrict__ 
 #pragma unroll
     for (int g = 0; g < 4; ++g) load_group(g, at);
   }
+  lds_barrier();  // the cleared words: a wave reports nonzero inputs before the first item's own barrier
   for (int w = blockIdx.x; w < items; w += gridDim.x) {
     const int t = w / ch.nchunks, c = w % ch.nchunks;
     const int nvalid = min(B, R - t * B);

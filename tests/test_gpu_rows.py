@@ -152,6 +152,19 @@ def test_lds_widths_lists(n, m, nl):
     run(n, layers, y0)
 
 
+@pytest.mark.parametrize("n,m", [(64, 9000), (1024, 9000), (2048, 4500), (4096, 2300)])
+def test_lds_widths_nonzero_inputs_of_one_wave(n, m):
+    """Every row has one nonzero input, at a neuron that the first or the last wave of its workgroup loads, and
+    some have none: each wave's report of them counts, those before the workgroup's first barrier too."""
+    rng = np.random.default_rng(n)
+    y0 = np.zeros((m, n), np.float32)
+    y0[np.arange(m), np.where(np.arange(m) % 2 == 0, n - 1, 0)] = 1.0
+    y0[rng.choice(m, size=m // 10, replace=False)] = 0.0
+    layers = [offset_layer(rng, n, -0.01) for _ in range(2)]
+    log(f"LDS widths, nonzero inputs: n={n} m={m}")
+    run(n, layers, y0)
+
+
 @pytest.mark.parametrize("n,m,scale", [(1024, 300, 1.0), (1024, 1, 1.0), (1000, 5000, 1.0), (6000, 700, 0.9), (6000, 60, 1.0)])
 def test_final_rows_in_any_order(n, m, scale):
     """Final activations for ids that are unsorted, repeated, dead and alive, the whole list of categories, one
