@@ -3463,7 +3463,8 @@ SegPack seg_order(int N, Src src, Deg deg, std::vector<uint16_t> *first) {
   // terms of column j in segment 0 (*first) and groups of 8 per segment: sources below N - kSegCap
   // have to be in segment 0, those from kSegCap in segment 1, and the cut is free between them: the
   // fewest groups, then the most even cut (one class of columns is one run length for its waves)
-  std::vector<uint32_t> key((size_t)N);
+  static_assert(kMaxDegree < 1 << 16, "a cut and a key hold numbers of sources and of groups in 16 bits");
+  std::vector<uint32_t> key((size_t)N);  // groups of both segments << 16 | groups of segment 0
   first->resize((size_t)N);
   for (int j = 0; j < N; ++j) {
     const int d = deg(j);
@@ -3489,7 +3490,7 @@ SegPack seg_order(int N, Src src, Deg deg, std::vector<uint16_t> *first) {
     }
     (*first)[(size_t)j] = (uint16_t)n0;
     const uint32_t a = (uint32_t)(n0 + 7) / 8, b = (uint32_t)(d - n0 + 7) / 8;
-    key[(size_t)j] = (a + b) * 1024u + a;
+    key[(size_t)j] = (a + b) << 16 | a;
   }
   // longest columns first (blocks go round the waves, so every wave gets some), stable, so that equal
   // columns stay in order and their outputs are consecutive
@@ -3510,8 +3511,8 @@ SegPack seg_order(int N, Src src, Deg deg, std::vector<uint16_t> *first) {
         for (int c = 0; c < 64; ++c) {
           const uint32_t j = p.col[(size_t)k * 64 + c];
           if (j == kNoColumn) continue;
-          const uint32_t a = key[j] % 1024u;
-          n = std::max(n, sg == 0 ? a : key[j] / 1024u - a);
+          const uint32_t a = key[j] & 0xffffu;
+          n = std::max(n, sg == 0 ? a : (key[j] >> 16) - a);
         }
         p.desc[(size_t)sg * nb + k] = make_int2((int)p.groups, (int)n);
         p.groups += n;

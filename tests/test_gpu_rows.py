@@ -67,6 +67,22 @@ def test_rows_layers(n, m, kind):
     run(n, layers, y0)
 
 
+@pytest.mark.parametrize("n,where", [(4200, "first"), (CAP, "spread"), (CAP + 1, "first"), (16384, "last"), (16384, "spread")])
+def test_rows_longest_column(n, where):
+    """A column of 4096 sources, the most that the interface takes, beside columns of up to 8: one segment, and two
+    with all of its sources in one of them or in both."""
+    rng = np.random.default_rng(n)
+    deg = rng.integers(0, 9, size=n)
+    cols = [rng.choice(n, size=d, replace=False) for d in deg]
+    cols[n // 3] = {"first": np.arange(4096), "last": np.arange(n - 4096, n),
+                    "spread": rng.choice(n, size=4096, replace=False)}[where]
+    cp, ri, v = csc(rng, n, cols, 0.3)
+    v[cp[n // 3]:cp[n // 3 + 1]] *= np.float32(0.002)  # its sum stays below the upper limit
+    y0 = rng.random((6, n)).astype(np.float32)
+    log(f"rows, longest column n={n} {where}")
+    run(n, [(cp, ri, v, np.full(n, -0.2, np.float32))], y0)
+
+
 @pytest.mark.parametrize("seq", [(32, 40, 32), (40, 32, 40), (40, 40, 32)])
 @pytest.mark.parametrize("m", [90, 700])
 def test_rows_between_tiles(seq, m):
