@@ -44,7 +44,7 @@ typedef struct sdnn_net sdnn_net;
 typedef enum {
   SDNN_OK = 0,
   SDNN_EINVAL = 1,  /* an argument is malformed or out of range */
-  SDNN_ENOMEM = 2,  /* a device or host allocation failed (only sdnn_create / sdnn_load_layers) */
+  SDNN_ENOMEM = 2,  /* an allocation failed: of device memory (only sdnn_load_layers) or of host memory */
   SDNN_EDEVICE = 3, /* a HIP call failed; the handle is poisoned */
   SDNN_ESTATE = 4,  /* call out of order (e.g. infer before every layer is loaded) */
   SDNN_ERANGE = 5   /* output capacity too small; the needed size is reported */

@@ -42,6 +42,8 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <exception>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -63,9 +65,17 @@ sdnn_status fail(sdnn_status s, const char *fmt, ...) {
   va_start(ap, fmt);
   vsnprintf(buf, sizeof buf, fmt, ap);
   va_end(ap);
-  g_err = buf;
+  try {
+    g_err = buf;
+  } catch (...) {
+    g_err.clear();
+  }
   return s;
 }
+
+// The answer of an entry point in which an allocation on the host failed: no exception crosses the ABI.
+sdnn_status no_memory() { return fail(SDNN_ENOMEM, "out of host memory"); }
+#define SDNN_CATCH catch (...) { return no_memory(); }
 
 constexpr int kMaxNeurons = 65536;
 constexpr int kMaxLayers = 1000000;
@@ -77,21 +87,31 @@ constexpr int64_t kEncodeMinRows = 2048;   // live rows from which a fp32-input 
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// Run f(i) for i in [0, n) on up to 16 host threads (used for host-side validation and packing).
+// Run f(i) for i in [0, n) on up to 16 host threads, the caller's among them (used for host-side validation and
+// packing). What f throws (out of memory) stops all of them and is thrown on the caller's thread; threads
+// that cannot be started are done without.
 template <class F>
 void parallel_for(int32_t n, F f) {
   const int32_t nt = std::max<int32_t>(1, std::min<int32_t>({n, 16, (int32_t)std::max(1u, std::thread::hardware_concurrency())}));
-  if (nt == 1) {
-    for (int32_t i = 0; i < n; ++i) f(i);
-    return;
-  }
   std::atomic<int32_t> next{0};
+  std::atomic<bool> failed{false};
+  std::exception_ptr thrown;  // by the thread that set failed first; read after the joins
+  auto work = [&]() noexcept {
+    try {
+      for (int32_t i = next++; i < n && !failed; i = next++) f(i);
+    } catch (...) {
+      if (!failed.exchange(true)) thrown = std::current_exception();
+    }
+  };
   std::vector<std::thread> th;
-  for (int32_t t = 0; t < nt; ++t)
-    th.emplace_back([&]() {
-      for (int32_t i = next++; i < n; i = next++) f(i);
-    });
+  try {
+    th.reserve((size_t)nt - 1);
+    for (int32_t t = 1; t < nt; ++t) th.emplace_back(work);
+  } catch (...) {
+  }
+  work();
   for (auto &x : th) x.join();
+  if (thrown) std::rethrow_exception(thrown);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -4189,14 +4209,13 @@ extern "C" {
 
 const char *sdnn_last_error(void) { return g_err.c_str(); }
 
-sdnn_status sdnn_create(sdnn_net **out, int32_t n_neurons, int32_t n_layers, float ymax) {
+sdnn_status sdnn_create(sdnn_net **out, int32_t n_neurons, int32_t n_layers, float ymax) try {
   if (!out) return fail(SDNN_EINVAL, "out is null");
   *out = nullptr;
   if (n_neurons < 1 || n_neurons > kMaxNeurons) return fail(SDNN_EINVAL, "n_neurons %d not in [1, %d]", n_neurons, kMaxNeurons);
   if (n_layers < 1 || n_layers > kMaxLayers) return fail(SDNN_EINVAL, "n_layers %d not in [1, %d]", n_layers, kMaxLayers);
   if (!std::isfinite(ymax) || !(ymax > 0.0f)) return fail(SDNN_EINVAL, "ymax must be finite and > 0");
-  sdnn_net *net = new (std::nothrow) sdnn_net;
-  if (!net) return fail(SDNN_ENOMEM, "out of host memory");
+  auto net = std::make_unique<sdnn_net>();
   net->N = n_neurons;
   net->L = n_layers;
   net->ymax = ymax;
@@ -4213,10 +4232,10 @@ sdnn_status sdnn_create(sdnn_net **out, int32_t n_neurons, int32_t n_layers, flo
     // layer 0 from bit tiles: 32-row tiles while their words fit 64 KiB of LDS, else 16-row tiles
     net->bitsT = (size_t)n_neurons * 4 <= 64 * 1024 ? 32 : ((size_t)n_neurons * 2 <= 128 * 1024 ? 16 : 0);
   }
-  *out = net;
+  *out = net.release();
   g_err.clear();
   return SDNN_OK;
-}
+} SDNN_CATCH
 
 int32_t sdnn_kernel_path(const sdnn_net *net) { return net ? net->path : -1; }
 
@@ -4231,7 +4250,7 @@ sdnn_status sdnn_enable_equal_value_kernels(sdnn_net *net, int32_t enable) {
 }
 
 sdnn_status sdnn_load_layers(sdnn_net *net, int32_t l0, int32_t nl, const int64_t *col_ptr, const int32_t *row_idx,
-                             const float *val, const float *bias, void *hip_stream) {
+                             const float *val, const float *bias, void *hip_stream) try {
   sdnn_status st = check_usable(net);
   if (st != SDNN_OK) return st;
   if (nl < 1 || l0 < 0 || (int64_t)l0 + nl > net->L) return fail(SDNN_EINVAL, "layers [%d, %d) outside [0, %d)", l0, l0 + nl, net->L);
@@ -4854,7 +4873,7 @@ sdnn_status sdnn_load_layers(sdnn_net *net, int32_t l0, int32_t nl, const int64_
   net->n_loaded += nl;
   g_err.clear();
   return SDNN_OK;
-}
+} SDNN_CATCH
 
 size_t sdnn_workspace_bytes(const sdnn_net *net, int64_t n_rows) {
   if (!net || n_rows < 0) return 0;
@@ -5489,11 +5508,11 @@ sdnn_status infer_impl(sdnn_net *net, const float *y0, int64_t n_rows, void *wor
 }  // namespace
 
 sdnn_status sdnn_infer(sdnn_net *net, const float *y0, int64_t n_rows, void *workspace, size_t workspace_bytes,
-                       void *hip_stream) {
+                       void *hip_stream) try {
   return infer_impl(net, y0, n_rows, workspace, workspace_bytes, hip_stream);
-}
+} SDNN_CATCH
 
-sdnn_status sdnn_infer_static(sdnn_net *net, const float *y0, int64_t n_rows, void *hip_stream) {
+sdnn_status sdnn_infer_static(sdnn_net *net, const float *y0, int64_t n_rows, void *hip_stream) try {
   sdnn_status st = check_usable(net);
   if (st != SDNN_OK) return st;
   if (n_rows < 0) return fail(SDNN_EINVAL, "n_rows %lld out of range", (long long)n_rows);
@@ -5507,7 +5526,7 @@ sdnn_status sdnn_infer_static(sdnn_net *net, const float *y0, int64_t n_rows, vo
   st = scratch_address(dev, &ws);
   if (st != SDNN_OK) return st;
   return infer_impl(net, y0, n_rows, ws, kStaticWorkspaceBytes, hip_stream);
-}
+} SDNN_CATCH
 
 
 namespace {
@@ -5647,7 +5666,7 @@ sdnn_status sdnn_categories(sdnn_net *net, int64_t *ids, int64_t capacity, int64
   return SDNN_OK;
 }
 
-sdnn_status sdnn_live_counts(sdnn_net *net, int64_t *counts) {
+sdnn_status sdnn_live_counts(sdnn_net *net, int64_t *counts) try {
   sdnn_status st = check_usable(net);
   if (st != SDNN_OK) return st;
   if (!net->ran) return fail(SDNN_ESTATE, "no inference has run");
@@ -5675,9 +5694,9 @@ sdnn_status sdnn_live_counts(sdnn_net *net, int64_t *counts) {
   for (int32_t l = 1; l <= net->L; ++l) counts[l] = c[(size_t)l];
   g_err.clear();
   return SDNN_OK;
-}
+} SDNN_CATCH
 
-sdnn_status sdnn_final_rows(sdnn_net *net, const int64_t *ids, int64_t n, float *out_host) {
+sdnn_status sdnn_final_rows(sdnn_net *net, const int64_t *ids, int64_t n, float *out_host) try {
   sdnn_status st = check_usable(net);
   if (st != SDNN_OK) return st;
   if (!net->ran) return fail(SDNN_ESTATE, "no inference has run");
@@ -5772,9 +5791,9 @@ sdnn_status sdnn_final_rows(sdnn_net *net, const int64_t *ids, int64_t n, float 
     }
   g_err.clear();
   return SDNN_OK;
-}
+} SDNN_CATCH
 
-sdnn_status sdnn_set_profiling(sdnn_net *net, int32_t enable) {
+sdnn_status sdnn_set_profiling(sdnn_net *net, int32_t enable) try {
   sdnn_status st = check_usable(net);
   if (st != SDNN_OK) return st;
   if (enable < 0 || enable > 2) return fail(SDNN_EINVAL, "profiling mode %d is not 0, 1 or 2", enable);
@@ -5785,8 +5804,8 @@ sdnn_status sdnn_set_profiling(sdnn_net *net, int32_t enable) {
     return SDNN_OK;
   }
   if (net->prof_start.empty()) {
-    net->prof_start.resize((size_t)net->L);
     net->prof_end.resize((size_t)net->L);
+    net->prof_start.resize((size_t)net->L);
     for (int32_t l = 0; l < net->L; ++l) {
       HIP_OR_POISON(net, hipEventCreate(&net->prof_start[(size_t)l]));
       HIP_OR_POISON(net, hipEventCreate(&net->prof_end[(size_t)l]));
@@ -5798,7 +5817,7 @@ sdnn_status sdnn_set_profiling(sdnn_net *net, int32_t enable) {
   net->prof_mode = enable;
   g_err.clear();
   return SDNN_OK;
-}
+} SDNN_CATCH
 
 sdnn_status sdnn_layer_info(sdnn_net *net, int32_t *kernel, int32_t *launches) {
   sdnn_status st = check_usable(net);
