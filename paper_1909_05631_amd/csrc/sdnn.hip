@@ -3465,27 +3465,27 @@ struct LayerDev {
   const uint2 *segcol = nullptr;
 };
 
-// A layer's columns in the order and grouping of k_layer_seg: blocks of 64 columns, each with its
-// groups of 8 terms per segment.
-struct SegPack {
-  std::vector<uint32_t> col;      // column of position p, kNoColumn past the last
-  std::vector<int2> desc;         // [S][blocks]: first group, groups
-  size_t groups = 0;
-};
+// A layer's columns as k_layer_seg reads them: blocks of 64 columns, each with its groups of 8 terms per
+// segment. Formed in the pass that writes the layer's ELL, its sources in the caches. Loading without /
+// with the streams (ms): 96 layers of 16384 neurons, 32 sources, 211 / 209; 1 to 48 sources 202 / 206; 24
+// loads of one such layer of 4100 neurons 9.6 / 10.8 (passes, a sort and an upload of their own: 217, 216, 14.0).
 int seg_segments(int N) { return N <= kSegCap ? 1 : 2; }
 int seg_blocks(int N) { return (N + 63) / 64; }
 int seg_positions(int N) { return (int)align_up((size_t)N, kSegThreads); }
 
-// src(j, i): source i of column j, ascending; deg(j): its number of sources.
+// src(j, i): source i of column j, ascending; deg(j): its number of sources. Written: desc [S][blocks], colb
+// and cut [positions] (see k_layer_seg and k_pack_seg). Returns the number of groups.
 template <class Src, class Deg>
-SegPack seg_order(int N, Src src, Deg deg, std::vector<uint16_t> *first) {
+size_t seg_order(int N, Src src, Deg deg, const float *bias, int2 *desc, uint2 *colb, uint32_t *cut) {
   const int S = seg_segments(N), nb = seg_blocks(N);
-  // terms of column j in segment 0 (*first) and groups of 8 per segment: sources below N - kSegCap
+  // terms of column j in segment 0 (first) and groups of 8 per segment: sources below N - kSegCap
   // have to be in segment 0, those from kSegCap in segment 1, and the cut is free between them: the
   // fewest groups, then the most even cut (one class of columns is one run length for its waves)
   static_assert(kMaxDegree < 1 << 16, "a cut and a key hold numbers of sources and of groups in 16 bits");
   std::vector<uint32_t> key((size_t)N);  // groups of both segments << 16 | groups of segment 0
-  first->resize((size_t)N);
+  std::vector<uint16_t> first((size_t)N);
+  uint32_t most = 0;
+  bool one_key = true;
   for (int j = 0; j < N; ++j) {
     const int d = deg(j);
     int n0 = d;
@@ -3508,36 +3508,52 @@ SegPack seg_order(int N, Src src, Deg deg, std::vector<uint16_t> *first) {
       for (int n = hi; n >= lo && n > hi - 8; --n)  // the cuts that fill segment 1's last group
         if ((d - n) % 8 == 0) take(n);
     }
-    (*first)[(size_t)j] = (uint16_t)n0;
+    first[(size_t)j] = (uint16_t)n0;
     const uint32_t a = (uint32_t)(n0 + 7) / 8, b = (uint32_t)(d - n0 + 7) / 8;
     key[(size_t)j] = (a + b) << 16 | a;
+    most = std::max(most, a + b);
+    one_key = one_key && key[(size_t)j] == key[0];
   }
   // longest columns first (blocks go round the waves, so every wave gets some), stable, so that equal
-  // columns stay in order and their outputs are consecutive
-  std::vector<int32_t> order((size_t)N);
-  for (int j = 0; j < N; ++j) order[(size_t)j] = j;
-  if (!std::all_of(key.begin(), key.end(), [&](uint32_t k) { return k == key[0]; }))
-    std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return key[(size_t)x] > key[(size_t)y]; });
-  SegPack p;
-  p.col.assign((size_t)seg_positions(N), kNoColumn);
-  for (int i = 0; i < N; ++i) p.col[(size_t)i] = (uint32_t)order[(size_t)i];
-  p.desc.resize((size_t)S * nb);
+  // columns stay in order and their outputs are consecutive: a place per (a + b, a <= a + b), from the largest
+  auto bucket = [](uint32_t k) { return (size_t)(k >> 16) * ((k >> 16) + 1) / 2 + (k & 0xffffu); };
+  std::vector<int32_t> place;
+  if (!one_key) {
+    place.assign((size_t)(most + 1) * (most + 2) / 2, 0);
+    for (int j = 0; j < N; ++j) ++place[bucket(key[(size_t)j])];
+    int32_t at = 0;
+    for (size_t q = place.size(); q-- > 0;) {
+      const int32_t n = place[q];
+      place[q] = at;
+      at += n;
+    }
+  }
+  for (int k = 0; k < S * nb; ++k) desc[k] = make_int2(0, 0);
+  for (int j = 0; j < N; ++j) {
+    const uint32_t k = key[(size_t)j], a = k & 0xffffu, b = (k >> 16) - a;
+    const int p = one_key ? j : place[bucket(k)]++;
+    uint32_t bits;
+    std::memcpy(&bits, &bias[j], sizeof bits);
+    colb[p] = make_uint2((uint32_t)j, bits);
+    cut[p] = first[(size_t)j] | ((uint32_t)deg(j) << 16);
+    desc[p / 64].y = std::max(desc[p / 64].y, (int)a);
+    if (S == 2) desc[nb + p / 64].y = std::max(desc[nb + p / 64].y, (int)b);
+  }
+  for (int p = N; p < seg_positions(N); ++p) {
+    colb[p] = make_uint2(kNoColumn, 0u);
+    cut[p] = 0u;
+  }
   // a wave's groups in the order it sums them: segment by segment, its blocks in turn (an empty
   // block's first group is that of the next one, which the kernel loads ahead)
+  size_t groups = 0;
   for (int w = 0; w < 16; ++w)
     for (int sg = 0; sg < S; ++sg)
       for (int k = w; k < nb; k += 16) {
-        uint32_t n = 0;
-        for (int c = 0; c < 64; ++c) {
-          const uint32_t j = p.col[(size_t)k * 64 + c];
-          if (j == kNoColumn) continue;
-          const uint32_t a = key[j] & 0xffffu;
-          n = std::max(n, sg == 0 ? a : (key[j] >> 16) - a);
-        }
-        p.desc[(size_t)sg * nb + k] = make_int2((int)p.groups, (int)n);
-        p.groups += n;
+        int2 &d = desc[sg * nb + k];
+        d.x = (int)groups;
+        groups += (size_t)d.y;
       }
-  return p;
+  return groups;
 }
 
 // Layers (from layer 0) that get an LDS row placement: the per-layer kernel runs the first layers
@@ -4362,12 +4378,15 @@ sdnn_status sdnn_load_layers(sdnn_net *net, int32_t l0, int32_t nl, const int64_
   const size_t ell_words = layer_off[(size_t)nl];
   const size_t ell_bytes = align_up(ell_words * sizeof(int2), 256);
   const size_t bias_bytes = (size_t)nl * N * sizeof(float);
-  std::vector<int2> host_ell;
-  try {
-    host_ell.resize(ell_words);
-  } catch (...) {
-    return fail(SDNN_ENOMEM, "out of host memory packing %zu bytes", ell_words * sizeof(int2));
-  }
+  // and, for widths of k_layer_seg, the description of its streams: [nl][seg_dwords] int2, then [nl][seg_cwords]
+  // columns with biases and [nl][seg_cwords] cuts (the device writes the streams from the ELL and these)
+  const bool seg = net->path == 1 && N <= kSegMaxNeurons && !net->equal_value_kernels;
+  const size_t seg_dwords = (size_t)seg_segments(N) * seg_blocks(N), seg_cwords = (size_t)seg_positions(N);
+  const size_t seg_colb = align_up((size_t)nl * seg_dwords * sizeof(int2), 256);
+  const size_t seg_cut = seg_colb + (size_t)nl * seg_cwords * sizeof(uint2);
+  std::vector<char> hseg(seg ? seg_cut + (size_t)nl * seg_cwords * sizeof(uint32_t) : 0);
+  std::vector<size_t> groups((size_t)nl, 0);
+  std::vector<int2> host_ell(ell_words);
   parallel_for(nl, [&](int32_t i) {
     const int64_t *cp = col_ptr + (size_t)i * (N + 1);
     const int Ki = K[(size_t)i];
@@ -4381,6 +4400,12 @@ sdnn_status sdnn_load_layers(sdnn_net *net, int32_t l0, int32_t nl, const int64_
       }
       for (; s < Ki; ++s) base[(size_t)s * N + j] = make_int2(0, 0);
     }
+    if (seg)
+      groups[(size_t)i] = seg_order(
+          N, [&](int j, int t) { return row_idx[cp[j] + t]; }, [&](int j) { return (int)(cp[j + 1] - cp[j]); },
+          bias + (size_t)i * N, reinterpret_cast<int2 *>(hseg.data()) + (size_t)i * seg_dwords,
+          reinterpret_cast<uint2 *>(hseg.data() + seg_colb) + (size_t)i * seg_cwords,
+          reinterpret_cast<uint32_t *>(hseg.data() + seg_cut) + (size_t)i * seg_cwords);
   });
   // ---- device copy
   if (net->device < 0) {
@@ -4436,8 +4461,38 @@ sdnn_status sdnn_load_layers(sdnn_net *net, int32_t l0, int32_t nl, const int64_
     HIP_OR_POISON(net, hipMemcpy(m0, hw0.data(), n0 * sizeof(int2), hipMemcpyHostToDevice));
     net->layers[0].ellw = reinterpret_cast<const int2 *>(m0);
   }
+  // the streams of k_layer_seg (one more group after each layer's: the kernel loads one ahead)
+  char *mg = nullptr;
+  size_t gbytes = 0;
+  std::vector<size_t> goff((size_t)nl + 1, 0);
+  if (seg) {
+    for (int32_t i = 0; i < nl; ++i) goff[(size_t)i + 1] = goff[(size_t)i] + groups[(size_t)i] + 1;
+    gbytes = goff[(size_t)nl] * kSegGroupWords * sizeof(uint4);
+    e = hipMalloc(reinterpret_cast<void **>(&mg), gbytes + hseg.size());
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      return fail(SDNN_ENOMEM, "hipMalloc of %zu bytes failed: %s", gbytes + hseg.size(), hipGetErrorString(e));
+    }
+    net->allocations.push_back(mg);
+  }
+  // (nothing is allocated on the host while these copies run)
   HIP_OR_POISON(net, hipMemcpyAsync(mem, host_ell.data(), ell_words * sizeof(int2), hipMemcpyHostToDevice, s));
   HIP_OR_POISON(net, hipMemcpyAsync(mem + ell_bytes, bias, bias_bytes, hipMemcpyHostToDevice, s));
+  if (mg) {
+    HIP_OR_POISON(net, hipMemcpyAsync(mg + gbytes, hseg.data(), hseg.size(), hipMemcpyHostToDevice, s));
+    for (int32_t i = 0; i < nl; ++i) {
+      LayerDev &ld = net->layers[(size_t)l0 + i];
+      ld.seg = reinterpret_cast<const uint4 *>(mg) + goff[(size_t)i] * kSegGroupWords;
+      ld.segdesc = reinterpret_cast<const int2 *>(mg + gbytes) + (size_t)i * seg_dwords;
+      ld.segcol = reinterpret_cast<const uint2 *>(mg + gbytes + seg_colb) + (size_t)i * seg_cwords;
+      hipLaunchKernelGGL(k_pack_seg, dim3(seg_blocks(N)), dim3(256), 0, s,
+                         reinterpret_cast<const int2 *>(mem) + layer_off[(size_t)i], N, seg_segments(N), stride,
+                         ld.segdesc, ld.segcol,
+                         reinterpret_cast<const unsigned *>(mg + gbytes + seg_cut) + (size_t)i * seg_cwords,
+                         seg_blocks(N), reinterpret_cast<uint4 *>(mg) + goff[(size_t)i] * kSegGroupWords);
+      HIP_OR_POISON(net, hipGetLastError());
+    }
+  }
   HIP_OR_POISON(net, hipStreamSynchronize(s));
   for (int32_t i = 0; i < nl; ++i) {
     LayerDev &ld = net->layers[(size_t)l0 + i];
@@ -4496,68 +4551,6 @@ sdnn_status sdnn_load_layers(sdnn_net *net, int32_t l0, int32_t nl, const int64_
         if (!ld.uniform) ld.w32 = reinterpret_cast<const float *>(ms + sbytes) + woff[q];
       }
     }
-  }
-  if (net->path == 1 && N <= kSegMaxNeurons && !net->equal_value_kernels) {
-    // the layers as k_layer_seg reads them: groups, descriptions and column order of each
-    std::vector<SegPack> packs((size_t)nl);
-    std::vector<std::vector<uint16_t>> first((size_t)nl);
-    auto src_of = [&](int32_t i) {
-      return [row_idx, cp = col_ptr + (size_t)i * (N + 1)](int j, int t) { return row_idx[cp[j] + t]; };
-    };
-    auto deg_of = [&](int32_t i) {
-      return [cp = col_ptr + (size_t)i * (N + 1)](int j) { return (int)(cp[j + 1] - cp[j]); };
-    };
-    parallel_for(nl, [&](int32_t i) { packs[(size_t)i] = seg_order(N, src_of(i), deg_of(i), &first[(size_t)i]); });
-    // (one more group after each layer's: the kernel loads one ahead)
-    std::vector<size_t> off((size_t)nl + 1, 0);
-    for (int32_t i = 0; i < nl; ++i) off[(size_t)i + 1] = off[(size_t)i] + packs[(size_t)i].groups + 1;
-    const size_t gbytes = off[(size_t)nl] * kSegGroupWords * sizeof(uint4);
-    // then the descriptions [nl][dwords], the columns and biases and the cuts [nl][cwords]
-    const size_t dwords = packs[0].desc.size(), cwords = (size_t)seg_positions(N);
-    const size_t dbytes = align_up((size_t)nl * dwords * sizeof(int2), 256);
-    const size_t cbytes = dbytes + (size_t)nl * cwords * sizeof(uint2);
-    std::vector<char> hd;
-    try {
-      hd.resize(cbytes + (size_t)nl * cwords * sizeof(uint32_t));
-    } catch (...) {
-      return fail(SDNN_ENOMEM, "out of host memory packing %d layers", nl);
-    }
-    parallel_for(nl, [&](int32_t i) {
-      const SegPack &p = packs[(size_t)i];
-      const auto deg = deg_of(i);
-      std::memcpy(hd.data() + (size_t)i * dwords * sizeof(int2), p.desc.data(), dwords * sizeof(int2));
-      uint2 *cb = reinterpret_cast<uint2 *>(hd.data() + dbytes) + (size_t)i * cwords;
-      uint32_t *cut = reinterpret_cast<uint32_t *>(hd.data() + cbytes) + (size_t)i * cwords;
-      for (size_t q = 0; q < cwords; ++q) {
-        uint32_t b = 0u;
-        cut[q] = 0u;
-        if (p.col[q] != kNoColumn) {
-          std::memcpy(&b, &bias[(size_t)i * N + p.col[q]], sizeof(uint32_t));
-          cut[q] = first[(size_t)i][p.col[q]] | ((uint32_t)deg((int)p.col[q]) << 16);
-        }
-        cb[q] = make_uint2(p.col[q], b);
-      }
-    });
-    char *mg = nullptr;
-    e = hipMalloc(reinterpret_cast<void **>(&mg), gbytes + hd.size());
-    if (e != hipSuccess) {
-      (void)hipGetLastError();
-      return fail(SDNN_ENOMEM, "hipMalloc of %zu bytes failed: %s", gbytes + hd.size(), hipGetErrorString(e));
-    }
-    net->allocations.push_back(mg);
-    HIP_OR_POISON(net, hipMemcpy(mg + gbytes, hd.data(), hd.size(), hipMemcpyHostToDevice));
-    for (int32_t i = 0; i < nl; ++i) {
-      LayerDev &ld = net->layers[(size_t)l0 + i];
-      ld.seg = reinterpret_cast<const uint4 *>(mg) + off[(size_t)i] * kSegGroupWords;
-      ld.segdesc = reinterpret_cast<const int2 *>(mg + gbytes) + (size_t)i * dwords;
-      ld.segcol = reinterpret_cast<const uint2 *>(mg + gbytes + dbytes) + (size_t)i * cwords;
-      hipLaunchKernelGGL(k_pack_seg, dim3(seg_blocks(N)), dim3(256), 0, s, ld.ell, N, seg_segments(N), stride,
-                         ld.segdesc, ld.segcol,
-                         reinterpret_cast<const unsigned *>(mg + gbytes + cbytes) + (size_t)i * cwords, seg_blocks(N),
-                         reinterpret_cast<uint4 *>(mg) + off[(size_t)i] * kSegGroupWords);
-      HIP_OR_POISON(net, hipGetLastError());
-    }
-    HIP_OR_POISON(net, hipStreamSynchronize(s));
   }
   {
     // 16-bit source indices in groups of 8 per output ([4][N][8] u16, one 16-byte load per group):
