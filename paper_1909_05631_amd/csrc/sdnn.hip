@@ -3462,13 +3462,13 @@ struct LayerDev {
   // columns as k_layer_seg reads them
   const uint4 *seg = nullptr;
   const int2 *segdesc = nullptr;
-  const uint2 *segcol = nullptr;
+  const uint2 *segcol = nullptr;  // (all null: no memory for them, the layer runs on tiles)
 };
 
 // A layer's columns as k_layer_seg reads them: blocks of 64 columns, each with its groups of 8 terms per
 // segment. Formed in the pass that writes the layer's ELL, its sources in the caches. Loading without /
 // with the streams (ms): 96 layers of 16384 neurons, 32 sources, 211 / 209; 1 to 48 sources 202 / 206; 24
-// loads of one such layer of 4100 neurons 9.6 / 10.8 (passes, a sort and an upload of their own: 217, 216, 14.0).
+// loads of one such layer of 4100 neurons 9.6 / 11.0 (with passes and a comparison sort of their own: 217, 216, 14.0).
 int seg_segments(int N) { return N <= kSegCap ? 1 : 2; }
 int seg_blocks(int N) { return (N + 63) / 64; }
 int seg_positions(int N) { return (int)align_up((size_t)N, kSegThreads); }
@@ -3648,6 +3648,8 @@ struct sdnn_net {
   // class (4 << c rows; class 0 also for 1 and 2 rows)
   LayerPtr *lp_dev[3] = {};
   int32_t n_loaded = 0;
+  std::vector<void *> streams;  // device allocations of segment streams (LayerDev::seg)
+  bool no_streams = false;      // their memory was needed for layers
   int32_t n_edge32 = 0;  // layers with grouped 32-source lists and per-edge weights (see k_layers_lds32)
   // last run
   bool ran = false;
@@ -4219,6 +4221,23 @@ hipError_t launch_layer(sdnn_net *net, int l, const float *yin, float *yout, con
   }
 }
 
+// Device memory that a load needs: where there is too little, the segment streams of earlier loads are given up.
+hipError_t device_alloc(sdnn_net *net, void **p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipSuccess || net->streams.empty()) return e;
+  (void)hipGetLastError();
+  for (LayerDev &ld : net->layers) {
+    ld.seg = nullptr;
+    ld.segdesc = nullptr;
+    ld.segcol = nullptr;
+  }
+  // (no run reads them: a network runs once all of its layers are loaded)
+  for (void *q : net->streams) (void)hipFree(q);
+  net->streams.clear();
+  net->no_streams = true;
+  return hipMalloc(p, bytes);
+}
+
 }  // namespace
 
 extern "C" {
@@ -4437,7 +4456,7 @@ sdnn_status sdnn_load_layers(sdnn_net *net, int32_t l0, int32_t nl, const int64_
     if (dev != net->device) return fail(SDNN_EINVAL, "current device %d differs from the handle's device %d", dev, net->device);
   }
   char *mem = nullptr;
-  hipError_t e = hipMalloc(reinterpret_cast<void **>(&mem), ell_bytes + bias_bytes);
+  hipError_t e = device_alloc(net, reinterpret_cast<void **>(&mem), ell_bytes + bias_bytes);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     return fail(SDNN_ENOMEM, "hipMalloc of %zu bytes failed: %s", ell_bytes + bias_bytes, hipGetErrorString(e));
@@ -4452,7 +4471,7 @@ sdnn_status sdnn_load_layers(sdnn_net *net, int32_t l0, int32_t nl, const int64_
     std::vector<int2> hw0(n0);
     for (size_t q = 0; q < n0; ++q) hw0[q] = make_int2(host_ell[q].x / stride * wsz, host_ell[q].y);
     char *m0 = nullptr;
-    e = hipMalloc(reinterpret_cast<void **>(&m0), std::max<size_t>(n0, 1) * sizeof(int2));
+    e = device_alloc(net, reinterpret_cast<void **>(&m0), std::max<size_t>(n0, 1) * sizeof(int2));
     if (e != hipSuccess) {
       (void)hipGetLastError();
       return fail(SDNN_ENOMEM, "hipMalloc of %zu bytes failed: %s", n0 * sizeof(int2), hipGetErrorString(e));
@@ -4461,38 +4480,9 @@ sdnn_status sdnn_load_layers(sdnn_net *net, int32_t l0, int32_t nl, const int64_
     HIP_OR_POISON(net, hipMemcpy(m0, hw0.data(), n0 * sizeof(int2), hipMemcpyHostToDevice));
     net->layers[0].ellw = reinterpret_cast<const int2 *>(m0);
   }
-  // the streams of k_layer_seg (one more group after each layer's: the kernel loads one ahead)
-  char *mg = nullptr;
-  size_t gbytes = 0;
-  std::vector<size_t> goff((size_t)nl + 1, 0);
-  if (seg) {
-    for (int32_t i = 0; i < nl; ++i) goff[(size_t)i + 1] = goff[(size_t)i] + groups[(size_t)i] + 1;
-    gbytes = goff[(size_t)nl] * kSegGroupWords * sizeof(uint4);
-    e = hipMalloc(reinterpret_cast<void **>(&mg), gbytes + hseg.size());
-    if (e != hipSuccess) {
-      (void)hipGetLastError();
-      return fail(SDNN_ENOMEM, "hipMalloc of %zu bytes failed: %s", gbytes + hseg.size(), hipGetErrorString(e));
-    }
-    net->allocations.push_back(mg);
-  }
   // (nothing is allocated on the host while these copies run)
   HIP_OR_POISON(net, hipMemcpyAsync(mem, host_ell.data(), ell_words * sizeof(int2), hipMemcpyHostToDevice, s));
   HIP_OR_POISON(net, hipMemcpyAsync(mem + ell_bytes, bias, bias_bytes, hipMemcpyHostToDevice, s));
-  if (mg) {
-    HIP_OR_POISON(net, hipMemcpyAsync(mg + gbytes, hseg.data(), hseg.size(), hipMemcpyHostToDevice, s));
-    for (int32_t i = 0; i < nl; ++i) {
-      LayerDev &ld = net->layers[(size_t)l0 + i];
-      ld.seg = reinterpret_cast<const uint4 *>(mg) + goff[(size_t)i] * kSegGroupWords;
-      ld.segdesc = reinterpret_cast<const int2 *>(mg + gbytes) + (size_t)i * seg_dwords;
-      ld.segcol = reinterpret_cast<const uint2 *>(mg + gbytes + seg_colb) + (size_t)i * seg_cwords;
-      hipLaunchKernelGGL(k_pack_seg, dim3(seg_blocks(N)), dim3(256), 0, s,
-                         reinterpret_cast<const int2 *>(mem) + layer_off[(size_t)i], N, seg_segments(N), stride,
-                         ld.segdesc, ld.segcol,
-                         reinterpret_cast<const unsigned *>(mg + gbytes + seg_cut) + (size_t)i * seg_cwords,
-                         seg_blocks(N), reinterpret_cast<uint4 *>(mg) + goff[(size_t)i] * kSegGroupWords);
-      HIP_OR_POISON(net, hipGetLastError());
-    }
-  }
   HIP_OR_POISON(net, hipStreamSynchronize(s));
   for (int32_t i = 0; i < nl; ++i) {
     LayerDev &ld = net->layers[(size_t)l0 + i];
@@ -4536,7 +4526,7 @@ sdnn_status sdnn_load_layers(sdnn_net *net, int32_t l0, int32_t nl, const int64_
       const size_t sbytes = align_up(hs.size() * sizeof(uint16_t), 256);
       const size_t wbytes = hw.size() * sizeof(float);
       char *ms = nullptr;
-      e = hipMalloc(reinterpret_cast<void **>(&ms), sbytes + wbytes);
+      e = device_alloc(net, reinterpret_cast<void **>(&ms), sbytes + wbytes);
       if (e != hipSuccess) {
         (void)hipGetLastError();
         return fail(SDNN_ENOMEM, "hipMalloc of %zu bytes failed: %s", sbytes + wbytes, hipGetErrorString(e));
@@ -4587,7 +4577,7 @@ sdnn_status sdnn_load_layers(sdnn_net *net, int32_t l0, int32_t nl, const int64_
       const size_t sbytes = align_up(h16.size() * sizeof(uint16_t), 256);
       const size_t wbytes = hw.size() * sizeof(float);
       char *m16 = nullptr;
-      e = hipMalloc(reinterpret_cast<void **>(&m16), sbytes + wbytes);
+      e = device_alloc(net, reinterpret_cast<void **>(&m16), sbytes + wbytes);
       if (e != hipSuccess) {
         (void)hipGetLastError();
         return fail(SDNN_ENOMEM, "hipMalloc of %zu bytes failed: %s", sbytes + wbytes, hipGetErrorString(e));
@@ -4620,7 +4610,7 @@ sdnn_status sdnn_load_layers(sdnn_net *net, int32_t l0, int32_t nl, const int64_
           for (size_t t = 0; t < per; ++t) po[t] = place[src[t]];
         });
         char *mp = nullptr;
-        e = hipMalloc(reinterpret_cast<void **>(&mp), hp.size() * sizeof(uint16_t));
+        e = device_alloc(net, reinterpret_cast<void **>(&mp), hp.size() * sizeof(uint16_t));
         if (e != hipSuccess) {
           (void)hipGetLastError();
           return fail(SDNN_ENOMEM, "hipMalloc of %zu bytes failed: %s", hp.size() * sizeof(uint16_t),
@@ -4674,7 +4664,7 @@ sdnn_status sdnn_load_layers(sdnn_net *net, int32_t l0, int32_t nl, const int64_
       const size_t cbytes = align_up(tot * sizeof(int32_t), 256);
       const size_t sbytes = align_up(hs.size() * sizeof(uint16_t), 256);
       char *mc = nullptr;
-      e = hipMalloc(reinterpret_cast<void **>(&mc), cbytes + 2 * sbytes);
+      e = device_alloc(net, reinterpret_cast<void **>(&mc), cbytes + 2 * sbytes);
       if (e != hipSuccess) {
         (void)hipGetLastError();
         return fail(SDNN_ENOMEM, "hipMalloc of %zu bytes failed: %s", cbytes + 2 * sbytes, hipGetErrorString(e));
@@ -4712,7 +4702,7 @@ sdnn_status sdnn_load_layers(sdnn_net *net, int32_t l0, int32_t nl, const int64_
       const std::vector<uint16_t> bp = D0 ? bank_balanced_lists(part.data(), D0, wbytes) : std::vector<uint16_t>();
       const size_t fb = align_up(bf.size() * sizeof(uint16_t), 256);
       char *mb = nullptr;
-      e = hipMalloc(reinterpret_cast<void **>(&mb), fb + bp.size() * sizeof(uint16_t));
+      e = device_alloc(net, reinterpret_cast<void **>(&mb), fb + bp.size() * sizeof(uint16_t));
       if (e != hipSuccess) {
         (void)hipGetLastError();
         return fail(SDNN_ENOMEM, "hipMalloc of %zu bytes failed: %s", fb + bp.size() * sizeof(uint16_t), hipGetErrorString(e));
@@ -4792,7 +4782,7 @@ sdnn_status sdnn_load_layers(sdnn_net *net, int32_t l0, int32_t nl, const int64_
       }
       if (bytes) {
         char *mg = nullptr;
-        e = hipMalloc(reinterpret_cast<void **>(&mg), bytes);
+        e = device_alloc(net, reinterpret_cast<void **>(&mg), bytes);
         if (e != hipSuccess) {
           (void)hipGetLastError();
           return fail(SDNN_ENOMEM, "hipMalloc of %zu bytes failed: %s", bytes, hipGetErrorString(e));
@@ -4832,7 +4822,7 @@ sdnn_status sdnn_load_layers(sdnn_net *net, int32_t l0, int32_t nl, const int64_
   // the device tables of layers (for launches that run several layers), one per tile-height class
   if (!net->lp_dev[0]) {
     LayerPtr *t = nullptr;
-    e = hipMalloc(reinterpret_cast<void **>(&t), (size_t)3 * net->L * sizeof(LayerPtr));
+    e = device_alloc(net, reinterpret_cast<void **>(&t), (size_t)3 * net->L * sizeof(LayerPtr));
     if (e != hipSuccess) {
       (void)hipGetLastError();
       return fail(SDNN_ENOMEM, "hipMalloc of the layer table failed: %s", hipGetErrorString(e));
@@ -4857,6 +4847,33 @@ sdnn_status sdnn_load_layers(sdnn_net *net, int32_t l0, int32_t nl, const int64_
         hp[(size_t)(l - t0)] = LayerPtr{ld.ell, e16, w8, ld.bias, cl, ld.w, ld.K, dd ? ld.D : N};
       }
       HIP_OR_POISON(net, hipMemcpy(net->lp_dev[c] + t0, hp.data(), hp.size() * sizeof(LayerPtr), hipMemcpyHostToDevice));
+    }
+  }
+  if (seg && !net->no_streams) {
+    // the streams of k_layer_seg, last, because the layers run without them where memory does not suffice
+    // (one more group after each layer's: the kernel loads one ahead)
+    std::vector<size_t> off((size_t)nl + 1, 0);
+    for (int32_t i = 0; i < nl; ++i) off[(size_t)i + 1] = off[(size_t)i] + groups[(size_t)i] + 1;
+    const size_t gbytes = off[(size_t)nl] * kSegGroupWords * sizeof(uint4);
+    net->streams.reserve(net->streams.size() + 1);
+    char *mg = nullptr;
+    if (hipMalloc(reinterpret_cast<void **>(&mg), gbytes + hseg.size()) != hipSuccess) {
+      (void)hipGetLastError();
+    } else {
+      net->streams.push_back(mg);
+      HIP_OR_POISON(net, hipMemcpyAsync(mg + gbytes, hseg.data(), hseg.size(), hipMemcpyHostToDevice, s));
+      for (int32_t i = 0; i < nl; ++i) {
+        LayerDev &ld = net->layers[(size_t)l0 + i];
+        ld.seg = reinterpret_cast<const uint4 *>(mg) + off[(size_t)i] * kSegGroupWords;
+        ld.segdesc = reinterpret_cast<const int2 *>(mg + gbytes) + (size_t)i * seg_dwords;
+        ld.segcol = reinterpret_cast<const uint2 *>(mg + gbytes + seg_colb) + (size_t)i * seg_cwords;
+        hipLaunchKernelGGL(k_pack_seg, dim3(seg_blocks(N)), dim3(256), 0, s, ld.ell, N, seg_segments(N), stride,
+                           ld.segdesc, ld.segcol,
+                           reinterpret_cast<const unsigned *>(mg + gbytes + seg_cut) + (size_t)i * seg_cwords,
+                           seg_blocks(N), reinterpret_cast<uint4 *>(mg) + off[(size_t)i] * kSegGroupWords);
+        HIP_OR_POISON(net, hipGetLastError());
+      }
+      HIP_OR_POISON(net, hipStreamSynchronize(s));
     }
   }
   for (int32_t i = 0; i < nl; ++i) {
@@ -5842,6 +5859,7 @@ void sdnn_destroy(sdnn_net *net) {
   for (auto &ev : net->prof_start) (void)hipEventDestroy(ev);
   for (auto &ev : net->prof_end) (void)hipEventDestroy(ev);
   for (void *p : net->allocations) (void)hipFree(p);
+  for (void *p : net->streams) (void)hipFree(p);
   for (auto &ev : net->events) (void)hipEventDestroy(ev);
   if (net->pinned) (void)hipHostFree(net->pinned);
   if (net->progress) (void)hipHostFree(net->progress);

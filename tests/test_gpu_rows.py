@@ -206,3 +206,48 @@ def test_final_rows_in_any_order(n, m, scale):
         np.testing.assert_array_equal(got, want)
     np.testing.assert_array_equal(gpu.net.categories(), cats)
     np.testing.assert_array_equal(gpu.net.live_counts(), oracle.padded_live_counts(o, 3))
+
+
+@pytest.mark.parametrize("left,rows", [(1.5, (True, False)), (0.5, (False, False))])
+def test_little_device_memory(left, rows):
+    """Layers whose segment streams don't fit the device's memory beside their lists load all the same, and run as
+    tiles; those loaded before them run as rows, unless the lists need their streams' memory."""
+    from tests.gpu_util import torch_cuda
+    torch = torch_cuda()
+    n, m, first, last = 16384, 300, 30, 40
+    rng = np.random.default_rng(12)
+    layers = []
+    for i in range(2):
+        cols = [np.sort(rng.choice(n, size=33, replace=False)) for _ in range(n)]
+        cp, ri, v = csc(rng, n, cols, 0.125)
+        layers.append((cp, ri, v, rng.uniform(-0.45, -0.35, size=n).astype(np.float32)))
+    y0 = rng.random((m, n)).astype(np.float32)
+    gpu = GpuNet(n, first + last)
+
+    def many(layer, k):
+        cp, ri, v, b = layer
+        return np.stack([cp + i * ri.size for i in range(k)]), np.tile(ri, k), np.tile(v, k), np.tile(b, (k, 1))
+
+    gpu.load(0, *many(layers[0], first))
+    yd = torch.from_numpy(y0).cuda()
+    nb = gpu.net.workspace_bytes(m)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    lists = last * n * (33 * 8 + 4)  # what the lists and biases take; the streams take about as much
+    torch.cuda.synchronize()
+    log(f"little device memory, {left} of the lists")
+    fill, leave = [], int(left * lists)
+    for _ in range(3):  # (the first report of free memory is low)
+        more = torch.cuda.mem_get_info()[0] - leave
+        if more > 32 << 20:
+            fill.append(torch.empty(more, dtype=torch.uint8, device="cuda"))
+    assert leave - (8 << 20) < torch.cuda.mem_get_info()[0] < leave + (40 << 20)
+    try:
+        gpu.load(first, *many(layers[1], last))
+    finally:
+        del fill
+        torch.cuda.empty_cache()
+    gpu.net.infer(yd, m, ws, nb, torch.cuda.current_stream())
+    cats = gpu.net.categories()
+    assert_parity(gpu, oracle_run(y0, [layers[0]] * first + [layers[1]] * last), cats)
+    launches = gpu.net.layer_info()[1]  # per layer of 300 rows: one launch on rows, two of 8 tiles
+    assert (launches[first - 1] == 1, launches[-1] == 1) == rows and cats.size
