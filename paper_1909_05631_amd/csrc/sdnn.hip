@@ -3758,7 +3758,7 @@ sdnn_status check_usable(const sdnn_net *net) {
 
 template <int B, int KC>
 hipError_t launch_lds(sdnn_net *net, const float *yin, float *yout, const LayerDev &ld, const int *ids,
-                      const int *count, int *rownz) {
+                      const int *count, int64_t rows, int *rownz) {
   static bool configured = false;
   const size_t lds = (size_t)B * net->N * sizeof(float);
   if (!configured) {
@@ -3774,7 +3774,17 @@ hipError_t launch_lds(sdnn_net *net, const float *yin, float *yout, const LayerD
   // distinct columns only, when the layer's duplicates need not be computed
   const bool dd = ld.ell16 && ld.ell16c && ld.cols && ld.dedup_ok;
   const bool placed = !dd && ld.place && ld.pell16;
-  if (!dd && ld.ell16 && ld.w8 && !ld.cols && net->N % 4 == 0) {
+  // k_layer_lds32 has one workgroup per CU, and its threads hold the rows of a tile of kLdsTileBytes: while it
+  // stages narrow tiles nothing else runs, and two workgroups of k_layer_lds overlap where a CU has more
+  // than one tile (narrower still, always). 60 layers, every row live, k_layer_lds / k_layer_lds32 (ms): 128
+  // neurons x 4500 rows (half a tile per CU) 1.15 / 1.47, x 60,000 4.78 / 5.04; 192 x 8000 1.75 / 1.69, x
+  // 150,000 (18 tiles per CU) 11.9 / 12.7; 256 x 20,000 2.82 / 3.03, x 60,000 6.09 / 6.22, x 150,000 15.1 / 13.9;
+  // 320 x 8300 2.08 / 2.39, x 20,000 3.37 / 3.37, x 60,000 7.50 / 7.15; 448 x 12,000 2.85 / 2.94, x 16,500 3.78 / 3.68.
+  const int64_t round = (int64_t)B * net->cus;  // rows of one tile per CU
+  const bool narrow = net->N <= 128 || (rows > round && (net->N <= 192 || (net->N <= 256 && rows <= 8 * round) ||
+                                                         (net->N <= 320 && rows <= 2 * round) ||
+                                                         (net->N <= 448 && 2 * rows <= 3 * round)));
+  if (!narrow && !dd && ld.ell16 && ld.w8 && !ld.cols && net->N % 4 == 0) {
     hipLaunchKernelGGL(k_layer_lds32<B>, dim3(net->cus), dim3(1024), lds, net->stream, yin, yout, net->N,
                        reinterpret_cast<const u32x4 *>(placed ? ld.pell16 : ld.ell16),
                        reinterpret_cast<const f32x4 *>(ld.w8), ld.bias, net->ymax, ids, count, net->masks, rownz,
@@ -3790,9 +3800,9 @@ hipError_t launch_lds(sdnn_net *net, const float *yin, float *yout, const LayerD
 
 template <int B>
 hipError_t launch_lds_k(sdnn_net *net, const float *yin, float *yout, const LayerDev &ld, const int *ids,
-                        const int *count, int *rownz) {
-  if (ld.K == 32) return launch_lds<B, 32>(net, yin, yout, ld, ids, count, rownz);
-  return launch_lds<B, 0>(net, yin, yout, ld, ids, count, rownz);
+                        const int *count, int64_t rows, int *rownz) {
+  if (ld.K == 32) return launch_lds<B, 32>(net, yin, yout, ld, ids, count, rows, rownz);
+  return launch_lds<B, 0>(net, yin, yout, ld, ids, count, rows, rownz);
 }
 
 // A layer of at most 8 tiles with K == 32 (see k_layer_gfm_small). Liveness goes to the partial
@@ -4210,14 +4220,14 @@ hipError_t launch_layers_lds(sdnn_net *net, const float *yin, float *yout, int l
   }
 }
 
-// One layer of the LDS-tile path.
+// One layer of the LDS-tile path, of at most `rows` live rows.
 hipError_t launch_layer(sdnn_net *net, int l, const float *yin, float *yout, const int *ids, const int *count,
-                        int *rownz) {
+                        int64_t rows, int *rownz) {
   const LayerDev &ld = net->layers[l];
   switch (net->B) {
-    case 32: return launch_lds_k<32>(net, yin, yout, ld, ids, count, rownz);
-    case 16: return launch_lds_k<16>(net, yin, yout, ld, ids, count, rownz);
-    default: return launch_lds_k<8>(net, yin, yout, ld, ids, count, rownz);
+    case 32: return launch_lds_k<32>(net, yin, yout, ld, ids, count, rows, rownz);
+    case 16: return launch_lds_k<16>(net, yin, yout, ld, ids, count, rows, rownz);
+    default: return launch_lds_k<8>(net, yin, yout, ld, ids, count, rows, rownz);
   }
 }
 
@@ -5035,7 +5045,8 @@ sdnn_status infer_lds(sdnn_net *net, const float *y0, int M) {
       }
     }
     if (!counted)
-      HIP_OR_POISON(net, launch_layer(net, l, yin, yout, net->ids[cur], net->counts + l, l == 0 ? net->rownz : nullptr));
+      HIP_OR_POISON(net, launch_layer(net, l, yin, yout, net->ids[cur], net->counts + l, live_bound,
+                                      l == 0 ? net->rownz : nullptr));
     if (rec) HIP_OR_POISON(net, hipEventRecord(net->prof_end[(size_t)l], s));
     net->layer_kernel[(size_t)l] = counted ? SDNN_KERNEL_BITS_COUNT : SDNN_KERNEL_LDS_TILE;
     net->layer_launches[(size_t)l] = counted ? 3 : 1;

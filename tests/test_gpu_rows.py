@@ -168,6 +168,17 @@ def test_lds_widths_lists(n, m, nl):
     run(n, layers, y0)
 
 
+@pytest.mark.parametrize("n,m", [(128, 1100), (132, 8192), (132, 8193), (192, 8193), (196, 65537), (256, 65536), (256, 65537),
+                                 (260, 16384), (320, 16385), (324, 8193), (448, 12288), (452, 8193)])
+def test_lds_widths_either_kernel(n, m):
+    """Both sides of the rule by width and rows between the per-layer kernels with one and two workgroups per
+    CU (256 CUs, 32 rows a tile)."""
+    rng = np.random.default_rng(n + m)
+    y0 = ((rng.random((m, n)) < rng.uniform(0.2, 0.9, size=(m, 1))) * rng.random((m, n))).astype(np.float32)
+    log(f"LDS widths, either kernel: n={n} m={m}")
+    run(n, [offset_layer(rng, n, -0.30) for _ in range(3)], y0)
+
+
 @pytest.mark.parametrize("n,m", [(64, 9000), (1024, 9000), (2048, 4500), (4096, 2300)])
 def test_lds_widths_nonzero_inputs_of_one_wave(n, m):
     """Every row has one nonzero input, at a neuron that the first or the last wave of its workgroup loads, and
