@@ -192,6 +192,26 @@ def test_lds_widths_nonzero_inputs_of_one_wave(n, m):
     run(n, layers, y0)
 
 
+@pytest.mark.parametrize("nl", [4095, 4096])
+def test_depth_of_the_read_back(nl):
+    """Live counts of networks that the host's words hold and of deeper ones."""
+    n, m = 32, 7
+    rng = np.random.default_rng(nl)
+    few = [offset_layer(rng, n, -0.01) for _ in range(3)]
+    y0 = rng.random((m, n)).astype(np.float32)
+    y0[2] = 0.0
+    layers = [few[l % 3] for l in range(nl)]
+    gpu = GpuNet(n, nl)
+    ri = few[0][1]
+    for l0 in range(0, nl, 512):
+        part = layers[l0:l0 + 512]
+        gpu.load(l0, np.stack([p[0] + i * ri.size for i, p in enumerate(part)]), np.concatenate([p[1] for p in part]),
+                 np.concatenate([p[2] for p in part]), np.stack([p[3] for p in part]))
+    log(f"{nl} layers")
+    cats = gpu.run(y0)
+    assert_parity(gpu, oracle_run(y0, layers), cats)
+
+
 @pytest.mark.parametrize("n,m,scale", [(1024, 300, 1.0), (1024, 1, 1.0), (1000, 5000, 1.0), (6000, 700, 0.9), (6000, 60, 1.0)])
 def test_final_rows_in_any_order(n, m, scale):
     """Final activations for ids that are unsorted, repeated, dead and alive, the whole list of categories, one
