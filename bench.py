@@ -354,6 +354,7 @@ def main() -> int:
         # (or the pack + layer pair) that the event pair of that layer spans
         ms, runs = net.layer_times()
         kind, launches = net.layer_info()
+        names = net.layer_kernels()
         per_run = ms / np.maximum(runs, 1)
         timed = [l for l in range(L) if runs[l] > 0]
         lay = max(timed, key=lambda l: per_run[l])
@@ -367,8 +368,8 @@ def main() -> int:
         nl = max(int(launches[lay]), 1)
         avg_launch_ms = float(per_run[lay]) / nl
         achieved = algo / nl / (avg_launch_ms * 1e-3) / 1e9
-        kname = sdnn.KERNEL_KINDS.get(int(kind[lay]), str(int(kind[lay])))
-        head = ", ".join(f"{l}:{per_run[l] * 1e3:.1f}us({sdnn.KERNEL_KINDS.get(int(kind[l]))} x{int(launches[l])}, "
+        kname = names[lay]
+        head = ", ".join(f"{l}:{per_run[l] * 1e3:.1f}us({names[l]} x{int(launches[l])}, "
                          f"R={int(counts[l])})" for l in timed[:6])
         log(f"large-layer kernel times: {head}")
         def timed_bytes(l):
@@ -418,8 +419,8 @@ def main() -> int:
         "live_edges_per_s": live_edges / t_step,
         "categories": int(cats.size),
         "live_counts_head": [int(c) for c in counts[:8]],
-        # kernel family of each of the first 8 layers of the last run (sdnn_layer_info)
-        "layer_kernels_head": [sdnn.KERNEL_KINDS.get(int(k), str(int(k))) for k in net.layer_info()[0][:8]],
+        # kernel of each of the first 8 layers of the last run (sdnn_layer_kernel)
+        "layer_kernels_head": net.layer_kernels()[:8],
     }
     print(json.dumps(out))
     return 0

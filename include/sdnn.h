@@ -151,7 +151,7 @@ sdnn_status sdnn_layer_times(sdnn_net *net, double *ms, int64_t *runs);
 /* Kernel families reported by sdnn_layer_info. */
 typedef enum {
   SDNN_KERNEL_NONE = 0,                 /* layer not run (every row had died) */
-  SDNN_KERNEL_LDS_TILE = 1,             /* activation tiles staged in LDS (k_layer_lds) */
+  SDNN_KERNEL_LDS_TILE = 1,             /* activation tiles staged in LDS (k_layer_lds, k_layer_lds32) */
   SDNN_KERNEL_GLOBAL_TILE = 2,          /* fp32 activations in global memory: feature-major tiles (k_layer_gfm) or,
                                            up to 16384 neurons, rows (k_layer_seg) */
   SDNN_KERNEL_GLOBAL_TILE_CODES = 3,    /* one-byte dictionary codes of the inputs (k_layer_gfm_u8) */
@@ -162,7 +162,7 @@ typedef enum {
                                            (k_pack_bits, k_count_dict, k_layer_count); only with
                                            sdnn_enable_equal_value_kernels */
   SDNN_KERNEL_LDS_FUSED = 8,            /* every layer from this one on, in one launch that keeps each
-                                           workgroup's rows in LDS (k_layers_lds); the launch is counted
+                                           workgroup's rows in LDS (k_layers_lds, k_layers_lds32); it is counted
                                            at its first layer, later layers report 0 launches */
   SDNN_KERNEL_GLOBAL_TILE_CODES16 = 9   /* two-byte dictionary codes of the inputs, for inputs of 257 to
                                            4096 distinct values (k_layer_gfm_u8 on 16-bit codes) */
@@ -173,6 +173,12 @@ typedef enum {
  * layers timed with events, the event pair spans these launches). kernel, launches: host arrays of
  * n_layers entries. */
 sdnn_status sdnn_layer_info(sdnn_net *net, int32_t *kernel, int32_t *launches);
+
+/* Diagnostics (untimed). The name of the kernel that ran `layer` of the last sdnn_infer, for families of more than
+ * one kernel the one it was: "k_layer_lds" or "k_layer_lds32" (SDNN_KERNEL_LDS_TILE), "k_layers_lds" or
+ * "k_layers_lds32" (SDNN_KERNEL_LDS_FUSED), "k_layer_gfm" or "k_layer_seg" (SDNN_KERNEL_GLOBAL_TILE);
+ * two kernels are joined by '+'. *name receives a string that is never freed. */
+sdnn_status sdnn_layer_kernel(sdnn_net *net, int32_t layer, const char **name);
 
 /* Free the handle and its device memory. NULL is a no-op. */
 void sdnn_destroy(sdnn_net *net);

@@ -3674,6 +3674,8 @@ struct sdnn_net {
   int final_list = 0;        // which ids buffer holds the final list
   int32_t layers_run = 0;    // layers enqueued by the last infer
   std::vector<int32_t> layer_kernel, layer_launches;  // per layer of the last infer (sdnn_layer_info)
+  // ... and whether it ran on k_layer_seg or a list-ahead kernel of that family (sdnn_layer_kernel)
+  std::vector<char> layer_ahead;
   const float *final_y = nullptr;   // path 0: final activations, row-major by row id
   const float *final_fm = nullptr;  // path 1: final activation tiles; live row i is at position src[final_list][i]
   bool final_rows_major = false;    // ... or rows by position (k_layer_seg's outputs)
@@ -3756,6 +3758,22 @@ sdnn_status check_usable(const sdnn_net *net) {
   return SDNN_OK;
 }
 
+// Whether a layer of at most `rows` live rows on widths staged in LDS runs on k_layer_lds32.
+bool lists_ahead(const sdnn_net *net, const LayerDev &ld, int64_t rows) {
+  if (!ld.ell16 || !ld.w8 || ld.cols || net->N % 4 != 0) return false;
+  // k_layer_lds32 has one workgroup per CU, and its threads hold the rows of a tile of kLdsTileBytes: while it
+  // stages narrow tiles nothing else runs, and two workgroups of k_layer_lds overlap where a CU has more
+  // than one tile (narrower still, always). 60 layers, every row live, k_layer_lds / k_layer_lds32 (ms): 128
+  // neurons x 4500 rows (half a tile per CU) 1.15 / 1.47, x 60,000 4.78 / 5.04; 192 x 8000 1.75 / 1.69, x
+  // 150,000 (18 tiles per CU) 11.9 / 12.7; 256 x 20,000 2.82 / 3.03, x 60,000 6.09 / 6.22, x 150,000 15.1 / 13.9;
+  // 320 x 8300 2.08 / 2.39, x 20,000 3.37 / 3.37, x 60,000 7.50 / 7.15; 448 x 12,000 2.85 / 2.94, x 16,500 3.78 / 3.68.
+  const int64_t round = (int64_t)net->B * net->cus;  // rows of one tile per CU
+  const bool narrow = net->N <= 128 || (rows > round && (net->N <= 192 || (net->N <= 256 && rows <= 8 * round) ||
+                                                         (net->N <= 320 && rows <= 2 * round) ||
+                                                         (net->N <= 448 && 2 * rows <= 3 * round)));
+  return !narrow;
+}
+
 template <int B, int KC>
 hipError_t launch_lds(sdnn_net *net, const float *yin, float *yout, const LayerDev &ld, const int *ids,
                       const int *count, int64_t rows, int *rownz) {
@@ -3774,17 +3792,7 @@ hipError_t launch_lds(sdnn_net *net, const float *yin, float *yout, const LayerD
   // distinct columns only, when the layer's duplicates need not be computed
   const bool dd = ld.ell16 && ld.ell16c && ld.cols && ld.dedup_ok;
   const bool placed = !dd && ld.place && ld.pell16;
-  // k_layer_lds32 has one workgroup per CU, and its threads hold the rows of a tile of kLdsTileBytes: while it
-  // stages narrow tiles nothing else runs, and two workgroups of k_layer_lds overlap where a CU has more
-  // than one tile (narrower still, always). 60 layers, every row live, k_layer_lds / k_layer_lds32 (ms): 128
-  // neurons x 4500 rows (half a tile per CU) 1.15 / 1.47, x 60,000 4.78 / 5.04; 192 x 8000 1.75 / 1.69, x
-  // 150,000 (18 tiles per CU) 11.9 / 12.7; 256 x 20,000 2.82 / 3.03, x 60,000 6.09 / 6.22, x 150,000 15.1 / 13.9;
-  // 320 x 8300 2.08 / 2.39, x 20,000 3.37 / 3.37, x 60,000 7.50 / 7.15; 448 x 12,000 2.85 / 2.94, x 16,500 3.78 / 3.68.
-  const int64_t round = (int64_t)B * net->cus;  // rows of one tile per CU
-  const bool narrow = net->N <= 128 || (rows > round && (net->N <= 192 || (net->N <= 256 && rows <= 8 * round) ||
-                                                         (net->N <= 320 && rows <= 2 * round) ||
-                                                         (net->N <= 448 && 2 * rows <= 3 * round)));
-  if (!narrow && !dd && ld.ell16 && ld.w8 && !ld.cols && net->N % 4 == 0) {
+  if (lists_ahead(net, ld, rows)) {
     hipLaunchKernelGGL(k_layer_lds32<B>, dim3(net->cus), dim3(1024), lds, net->stream, yin, yout, net->N,
                        reinterpret_cast<const u32x4 *>(placed ? ld.pell16 : ld.ell16),
                        reinterpret_cast<const f32x4 *>(ld.w8), ld.bias, net->ymax, ids, count, net->masks, rownz,
@@ -5010,6 +5018,7 @@ sdnn_status infer_lds(sdnn_net *net, const float *y0, int M) {
       if (net->profiling) net->prof_rec[(size_t)l] = rec;
       for (int32_t q = l; q < net->L; ++q) {
         net->layer_kernel[(size_t)q] = SDNN_KERNEL_LDS_FUSED;
+        net->layer_ahead[(size_t)q] = net->n_edge32 == net->L;
         net->layer_launches[(size_t)q] = q == l ? 1 : 0;
       }
       // the final list: positions still live after the last layer (bits per 32 positions)
@@ -5049,6 +5058,7 @@ sdnn_status infer_lds(sdnn_net *net, const float *y0, int M) {
                                       l == 0 ? net->rownz : nullptr));
     if (rec) HIP_OR_POISON(net, hipEventRecord(net->prof_end[(size_t)l], s));
     net->layer_kernel[(size_t)l] = counted ? SDNN_KERNEL_BITS_COUNT : SDNN_KERNEL_LDS_TILE;
+    net->layer_ahead[(size_t)l] = !counted && lists_ahead(net, net->layers[(size_t)l], live_bound);
     net->layer_launches[(size_t)l] = counted ? 3 : 1;
     if (net->profiling) net->prof_rec[(size_t)l] = rec;
     const unsigned long long tag = next_report_tag(net);
@@ -5273,6 +5283,7 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
         spread_used = true;
         fout_rows = true;
         net->layer_kernel[0] = SDNN_KERNEL_GLOBAL_TILE;
+        net->layer_ahead[0] = 1;
         net->layer_launches[0] = 1;
       } else {
         HIP_OR_POISON(net, launch_to_fm(net, y0, net->fm[0], net->ids[cur], npos + cur, try_bits ? nullptr : net->rownz));
@@ -5301,6 +5312,7 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
       spread_used = true;
       fout_rows = true;
       net->layer_kernel[(size_t)l] = SDNN_KERNEL_GLOBAL_TILE;
+      net->layer_ahead[(size_t)l] = 1;
       net->layer_launches[(size_t)l] = 1 + encode_tries;
     } else {
       // after a layer without compaction, this launch counts that layer's live rows
@@ -5409,6 +5421,7 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
         }
         spread_used = true;
         net->layer_kernel[0] = SDNN_KERNEL_GLOBAL_TILE;
+        net->layer_ahead[0] = lcur.seg != nullptr;
         net->layer_launches[0] = 2 + (lcur.seg ? 1 : gfm_launches(net, net->layers[0], tiles(P), 0));
         tag = next_report_tag(net);
         HIP_OR_POISON(net, compact(tag));
@@ -5610,6 +5623,7 @@ sdnn_status infer_impl(sdnn_net *net, const float *y0, int64_t n_rows, void *wor
   if (net->profiling) net->prof_rec.assign((size_t)net->L, 0);
   net->layer_kernel.assign((size_t)net->L, SDNN_KERNEL_NONE);
   net->layer_launches.assign((size_t)net->L, 0);
+  net->layer_ahead.assign((size_t)net->L, 0);
   st = net->path == 0 ? infer_lds(net, y0, M) : infer_gfm(net, y0, M);
   if (st != SDNN_OK) return st;
   net->ran = true;
@@ -5848,6 +5862,29 @@ sdnn_status sdnn_layer_info(sdnn_net *net, int32_t *kernel, int32_t *launches) {
   for (int32_t l = 0; l < net->L; ++l) {
     kernel[l] = net->layer_kernel[(size_t)l];
     launches[l] = net->layer_launches[(size_t)l];
+  }
+  g_err.clear();
+  return SDNN_OK;
+}
+
+sdnn_status sdnn_layer_kernel(sdnn_net *net, int32_t layer, const char **name) {
+  sdnn_status st = check_usable(net);
+  if (st != SDNN_OK) return st;
+  if (!net->ran) return fail(SDNN_ESTATE, "no inference has run");
+  if (!name) return fail(SDNN_EINVAL, "name is null");
+  if (layer < 0 || layer >= net->L) return fail(SDNN_EINVAL, "layer %d outside [0, %d)", layer, net->L);
+  const bool ahead = net->layer_ahead[(size_t)layer] != 0;
+  switch (net->layer_kernel[(size_t)layer]) {
+    case SDNN_KERNEL_LDS_TILE: *name = ahead ? "k_layer_lds32" : "k_layer_lds"; break;
+    case SDNN_KERNEL_GLOBAL_TILE: *name = ahead ? "k_layer_seg" : "k_layer_gfm"; break;
+    case SDNN_KERNEL_GLOBAL_TILE_CODES: *name = "k_layer_gfm_u8"; break;
+    case SDNN_KERNEL_GLOBAL_TILE_FEW_ROWS: *name = "k_layer_gfm_small"; break;
+    case SDNN_KERNEL_BITS: *name = "k_pack_bits+k_layer_bits"; break;
+    case SDNN_KERNEL_BITS_TO_CODES: *name = "k_pack_bits+k_layer_bits(codes)"; break;
+    case SDNN_KERNEL_BITS_COUNT: *name = "k_pack_bits+k_layer_count"; break;
+    case SDNN_KERNEL_LDS_FUSED: *name = ahead ? "k_layers_lds32" : "k_layers_lds"; break;
+    case SDNN_KERNEL_GLOBAL_TILE_CODES16: *name = "k_layer_gfm_u16"; break;
+    default: *name = "none"; break;
   }
   g_err.clear();
   return SDNN_OK;

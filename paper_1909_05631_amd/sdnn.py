@@ -16,8 +16,9 @@ EXPORTED_SYMBOLS = [
     "sdnn_create", "sdnn_load_layers", "sdnn_workspace_bytes", "sdnn_infer", "sdnn_categories",
     "sdnn_live_counts", "sdnn_final_rows", "sdnn_destroy", "sdnn_last_error", "sdnn_kernel_path",
     "sdnn_set_profiling", "sdnn_layer_times", "sdnn_layer_info", "sdnn_enable_equal_value_kernels",
-    "sdnn_infer_static",
+    "sdnn_infer_static", "sdnn_layer_kernel",
 ]
+# kernel families of sdnn_layer_info by a kernel of each (Net.layer_kernels names the kernel itself)
 KERNEL_KINDS = {0: "none", 1: "k_layer_lds", 2: "k_layer_gfm", 3: "k_layer_gfm_u8", 4: "k_layer_gfm_small",
                 5: "k_pack_bits+k_layer_bits", 6: "k_pack_bits+k_layer_bits(codes)", 7: "k_pack_bits+k_layer_count",
                 8: "k_layers_lds", 9: "k_layer_gfm_u16"}
@@ -61,9 +62,10 @@ def load_library():
         L.sdnn_layer_info.argtypes = [vp, vp, vp]
         L.sdnn_enable_equal_value_kernels.argtypes = [vp, i32]
         L.sdnn_infer_static.argtypes = [vp, vp, i64, vp]
+        L.sdnn_layer_kernel.argtypes = [vp, i32, ctypes.POINTER(ctypes.c_char_p)]
         for name in ("sdnn_create", "sdnn_load_layers", "sdnn_infer", "sdnn_categories", "sdnn_live_counts",
                      "sdnn_final_rows", "sdnn_set_profiling", "sdnn_layer_times", "sdnn_layer_info",
-                     "sdnn_enable_equal_value_kernels", "sdnn_infer_static"):
+                     "sdnn_enable_equal_value_kernels", "sdnn_infer_static", "sdnn_layer_kernel"):
             getattr(L, name).restype = ctypes.c_int
         _lib = L
     return _lib
@@ -177,6 +179,15 @@ class Net:
         launches = np.zeros(self.n_layers, dtype=np.int32)
         _check(load_library().sdnn_layer_info(self._h, _p(kind), _p(launches)))
         return kind, launches
+
+    def layer_kernels(self) -> list[str]:
+        """Per layer of the last run: the kernel that ran it."""
+        names = []
+        for l in range(self.n_layers):
+            name = ctypes.c_char_p()
+            _check(load_library().sdnn_layer_kernel(self._h, l, ctypes.byref(name)))
+            names.append(name.value.decode())
+        return names
 
     def layer_times(self) -> tuple[np.ndarray, np.ndarray]:
         ms = np.zeros(self.n_layers, dtype=np.float64)

@@ -136,3 +136,9 @@ def test_profiling_mode_out_of_range_is_einval():
         _check = sdnn.load_library().sdnn_set_profiling(net._h, 3)
         sdnn._check(_check)
     assert ei.value.name == "SDNN_EINVAL"
+
+
+def test_layer_kernel_before_a_run_is_a_state_error():
+    with pytest.raises(sdnn.SdnnError) as ei:
+        sdnn.Net(1024, 2).layer_kernels()
+    assert ei.value.name == "SDNN_ESTATE"

@@ -64,7 +64,14 @@ def test_rows_layers(n, m, kind):
         y0[m // 2] = 0.0
     log(f"rows n={n} m={m} {kind}")
     layers = [layer(rng, n, kind) for _ in range(3)]
-    run(n, layers, y0)
+    gpu, cats = run(n, layers, y0)
+    live = gpu.net.live_counts()
+    names = gpu.net.layer_kernels()
+    assert names[0] == "k_layer_seg"
+    few = False  # once in tiles, layers of 32 sources stay there
+    for l in (1, 2):
+        few = few or (kind != "ragged" and live[l] <= 256)
+        assert names[l] == ("none" if live[l] == 0 else "k_layer_gfm_small" if few else "k_layer_seg")
 
 
 @pytest.mark.parametrize("n,where", [(4200, "first"), (CAP, "spread"), (CAP + 1, "first"), (16384, "last"), (16384, "spread")])
@@ -100,6 +107,11 @@ def test_rows_between_tiles(seq, m):
     log(f"rows between tiles {seq} m={m}")
     gpu, cats = run(n, layers, y0)
     assert 0 < cats.size
+    live = gpu.net.live_counts()
+    assert live[2] > 256 or m == 90
+    few = "k_layer_gfm_small" if m == 90 else "k_layer_seg"
+    expect = ["k_pack_bits+k_layer_bits" if seq[0] == 32 else "k_layer_seg"]
+    assert gpu.net.layer_kernels() == expect + ["k_layer_seg" if k == 40 else few for k in seq[1:]]
 
 
 def test_rows_to_codes_and_back():
@@ -116,6 +128,7 @@ def test_rows_to_codes_and_back():
     from paper_1909_05631_amd import sdnn
     kinds = [sdnn.KERNEL_KINDS[int(k)] for k in gpu.net.layer_info()[0]]
     assert kinds == ["k_layer_gfm", "k_layer_gfm", "k_layer_gfm_u8", "k_layer_gfm"]
+    assert gpu.net.layer_kernels() == ["k_layer_seg", "k_layer_seg", "k_layer_gfm_u8", "k_layer_seg"]
     assert cats.size == m
 
 
@@ -165,18 +178,27 @@ def test_lds_widths_lists(n, m, nl):
     if nl > 60:  # every row but the strongest dies at layer 60
         layers[60] = (*layers[60][:3], np.full(n, -58.0, np.float32))
     log(f"LDS widths, lists ahead: n={n} m={m} layers={nl}")
-    run(n, layers, y0)
+    gpu, cats = run(n, layers, y0)
+    names = gpu.net.layer_kernels()
+    if m <= 1024:
+        assert names == ["k_layers_lds32"] * nl
+    else:
+        one = "k_layer_lds32" if n % 4 == 0 and n > 448 else "k_layer_lds"
+        assert names[0] == one and set(names) <= {one, "k_layers_lds32", "none"}
 
 
-@pytest.mark.parametrize("n,m", [(128, 1100), (132, 8192), (132, 8193), (192, 8193), (196, 65537), (256, 65536), (256, 65537),
-                                 (260, 16384), (320, 16385), (324, 8193), (448, 12288), (452, 8193)])
-def test_lds_widths_either_kernel(n, m):
+@pytest.mark.parametrize("n,m,ahead", [
+    (128, 1100, False), (132, 8192, True), (132, 8193, False), (192, 8193, False), (196, 65537, True), (256, 65536, False),
+    (256, 65537, True), (260, 16384, False), (320, 16385, True), (324, 8193, False), (448, 12288, False), (452, 8193, True),
+])
+def test_lds_widths_either_kernel(n, m, ahead):
     """Both sides of the rule by width and rows between the per-layer kernels with one and two workgroups per
     CU (256 CUs, 32 rows a tile)."""
     rng = np.random.default_rng(n + m)
     y0 = ((rng.random((m, n)) < rng.uniform(0.2, 0.9, size=(m, 1))) * rng.random((m, n))).astype(np.float32)
     log(f"LDS widths, either kernel: n={n} m={m}")
-    run(n, [offset_layer(rng, n, -0.30) for _ in range(3)], y0)
+    gpu, cats = run(n, [offset_layer(rng, n, -0.30) for _ in range(3)], y0)
+    assert gpu.net.layer_kernels()[0] == ("k_layer_lds32" if ahead else "k_layer_lds")
 
 
 @pytest.mark.parametrize("n,m", [(64, 9000), (1024, 9000), (2048, 4500), (4096, 2300)])
@@ -280,5 +302,5 @@ def test_little_device_memory(left, rows):
     gpu.net.infer(yd, m, ws, nb, torch.cuda.current_stream())
     cats = gpu.net.categories()
     assert_parity(gpu, oracle_run(y0, [layers[0]] * first + [layers[1]] * last), cats)
-    launches = gpu.net.layer_info()[1]  # per layer of 300 rows: one launch on rows, two of 8 tiles
-    assert (launches[first - 1] == 1, launches[-1] == 1) == rows and cats.size
+    names = gpu.net.layer_kernels()
+    assert (names[first - 1], names[-1]) == tuple("k_layer_seg" if r else "k_layer_gfm" for r in rows) and cats.size
