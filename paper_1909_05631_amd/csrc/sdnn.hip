@@ -3462,7 +3462,7 @@ struct LayerDev {
   // columns as k_layer_seg reads them
   const uint4 *seg = nullptr;
   const int2 *segdesc = nullptr;
-  const uint2 *segcol = nullptr;  // (all null: no memory for them, the layer runs on tiles)
+  const uint2 *segcol = nullptr;  // (null in every layer: no memory for them, the network runs on tiles)
 };
 
 // A layer's columns as k_layer_seg reads them: blocks of 64 columns, each with its groups of 8 terms per
@@ -4239,20 +4239,26 @@ hipError_t launch_layer(sdnn_net *net, int l, const float *yin, float *yout, con
   }
 }
 
-// Device memory that a load needs: where there is too little, the segment streams of earlier loads are given up.
-hipError_t device_alloc(sdnn_net *net, void **p, size_t bytes) {
-  hipError_t e = hipMalloc(p, bytes);
-  if (e == hipSuccess || net->streams.empty()) return e;
-  (void)hipGetLastError();
+// Gives up the segment streams of all layers, loaded and to come: a layer on rows leaves the liveness words of
+// the layer after it as they are, which those of few-row layers of other than 32 sources on tiles must not
+// be, so a network has all of its streams or none. (No run reads them: it needs every layer loaded.)
+void drop_streams(sdnn_net *net) {
   for (LayerDev &ld : net->layers) {
     ld.seg = nullptr;
     ld.segdesc = nullptr;
     ld.segcol = nullptr;
   }
-  // (no run reads them: a network runs once all of its layers are loaded)
   for (void *q : net->streams) (void)hipFree(q);
   net->streams.clear();
   net->no_streams = true;
+}
+
+// Device memory that a load needs: where there is too little, the segment streams of earlier loads are given up.
+hipError_t device_alloc(sdnn_net *net, void **p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipSuccess || net->streams.empty()) return e;
+  (void)hipGetLastError();
+  drop_streams(net);
   return hipMalloc(p, bytes);
 }
 
@@ -4877,6 +4883,7 @@ sdnn_status sdnn_load_layers(sdnn_net *net, int32_t l0, int32_t nl, const int64_
     char *mg = nullptr;
     if (hipMalloc(reinterpret_cast<void **>(&mg), gbytes + hseg.size()) != hipSuccess) {
       (void)hipGetLastError();
+      drop_streams(net);
     } else {
       net->streams.push_back(mg);
       HIP_OR_POISON(net, hipMemcpyAsync(mg + gbytes, hseg.data(), hseg.size(), hipMemcpyHostToDevice, s));

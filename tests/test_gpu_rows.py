@@ -3,6 +3,8 @@ and two LDS segments at their edges, the split of a column's sources between the
 outputs for few rows, and the ways its rows come from and go to the tile kernels."""
 from __future__ import annotations
 
+import gc
+
 import numpy as np
 import pytest
 
@@ -261,10 +263,10 @@ def test_final_rows_in_any_order(n, m, scale):
     np.testing.assert_array_equal(gpu.net.live_counts(), oracle.padded_live_counts(o, 3))
 
 
-@pytest.mark.parametrize("left,rows", [(1.5, (True, False)), (0.5, (False, False))])
-def test_little_device_memory(left, rows):
-    """Layers whose segment streams don't fit the device's memory beside their lists load all the same, and run as
-    tiles; those loaded before them run as rows, unless the lists need their streams' memory."""
+@pytest.mark.parametrize("left", [1.5, 0.5])
+def test_little_device_memory(left):
+    """Layers whose segment streams don't fit the device's memory beside their lists, or whose lists need the memory
+    of earlier layers' streams, load all the same; the network runs on tiles."""
     from tests.gpu_util import torch_cuda
     torch = torch_cuda()
     n, m, first, last = 16384, 300, 30, 40
@@ -288,12 +290,18 @@ def test_little_device_memory(left, rows):
     lists = last * n * (33 * 8 + 4)  # what the lists and biases take; the streams take about as much
     torch.cuda.synchronize()
     log(f"little device memory, {left} of the lists")
+    gc.collect()  # networks and tensors of earlier tests, and what torch keeps of them
+    torch.cuda.empty_cache()
     fill, leave = [], int(left * lists)
-    for _ in range(3):  # (the first report of free memory is low)
+    for _ in range(8):  # (the first reports of free memory are low, and torch may serve a piece from its own)
         more = torch.cuda.mem_get_info()[0] - leave
         if more > 32 << 20:
             fill.append(torch.empty(more, dtype=torch.uint8, device="cuda"))
-    assert leave - (8 << 20) < torch.cuda.mem_get_info()[0] < leave + (40 << 20)
+    free = torch.cuda.mem_get_info()[0]
+    if not leave - (8 << 20) < free < leave + (40 << 20):
+        del fill
+        torch.cuda.empty_cache()
+        pytest.skip(f"{free >> 20} MiB are free where {leave >> 20} were to be left")
     try:
         gpu.load(first, *many(layers[1], last))
     finally:
@@ -303,4 +311,4 @@ def test_little_device_memory(left, rows):
     cats = gpu.net.categories()
     assert_parity(gpu, oracle_run(y0, [layers[0]] * first + [layers[1]] * last), cats)
     names = gpu.net.layer_kernels()
-    assert (names[first - 1], names[-1]) == tuple("k_layer_seg" if r else "k_layer_gfm" for r in rows) and cats.size
+    assert names[1:] == ["k_layer_gfm"] * (first + last - 1) and cats.size
