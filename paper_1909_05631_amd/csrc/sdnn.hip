@@ -9,26 +9,29 @@
 // Data layout in HBM
 //   Activations: path 0 (widths whose tiles fit LDS, N <= 4096) keeps row-major [M][N] fp32 rows
 //   and a list of live row ids; path 1 keeps feature-major tiles of 32 list positions ([N][32] fp32
-//   per tile, 128 bytes per source), or after layer 0 one-byte dictionary codes in tiles of 64 or
-//   128 positions, or bit tiles of 16 or 32 positions for binary inputs.
+//   per tile, 128 bytes per source), up to 16384 neurons fp32 rows by list position, or after layer 0
+//   one-byte dictionary codes in tiles of 64 or 128 positions (two-byte ones past 32768 neurons), or bit
+//   tiles of 16 or 32 positions for binary inputs.
 //   Weights: per layer a slot-major ELL table [K][N] of (source offset, fp32 weight), entry [s][j]
 //   the s-th smallest source of output j, padded with (0, 0.0f); padding adds fma(y, 0, acc) = acc
 //   exactly. Layers with 32 sources per column also get 16-bit source lists with their fp32
 //   weights beside them: [32][N] u16 + [32][N] fp32 (path 1, six bytes per edge) and [4][N][8]
-//   u16 + fp32 (path 0, eight per 16-byte load). With the opt-in equal-value kernels, a layer whose
+//   u16 + [8][N][4] fp32 (path 0, 16-byte loads). Path 1 up to 16384 neurons also keeps every layer's
+//   columns as the streams of k_layer_seg. With the opt-in equal-value kernels, a layer whose
 //   weights and biases are all equal keeps one weight instead, and where columns share their list
 //   only the representative columns' lists.
 //
 // Kernels (every output is the ascending-source fma chain above, so every path gives the same bits)
-//   path 0: k_layer_lds (one layer; B rows staged in LDS as [k][B]), k_layers_lds (every remaining
-//     layer in one launch, each workgroup's rows resident in LDS), and, opt-in, layer 0 by counts
-//     of bit tiles.
+//   path 0: k_layer_lds32 (one layer; B rows staged in LDS as [k][B]) and k_layers_lds32 (every remaining
+//     layer in one launch, each workgroup's rows resident in LDS) for lists of 32 sources with per-edge
+//     weights, loaded ahead; k_layer_lds and k_layers_lds for other lists (and narrow batches); opt-in, layer
+//     0 by counts of bit tiles.
 //   path 1, layer 0: k_pack_bits, then k_layer_bits (or, opt-in for one-weight layers,
 //     k_count_dict + k_layer_count: adder-tree counts of set source bits, decoded by a
-//     dictionary); non-binary inputs take k_to_fm + k_layer_gfm.
-//   path 1, later layers: k_layer_gfm_u8 (code tiles in), k_layer_gfm (fp32 tiles in),
-//     k_layer_gfm_small (at most 8 tiles, whole chains in flight). Workgroups are mapped so that
-//     each XCD gathers from its own tile, resident in its L2.
+//     dictionary); non-binary inputs take k_layer_seg (up to 16384 neurons) or k_to_fm + k_layer_gfm.
+//   path 1, later layers: k_layer_gfm_u8 (code tiles in), k_layer_seg (fp32 rows in, up to 16384 neurons),
+//     k_layer_gfm (fp32 tiles in), k_layer_gfm_small (at most 8 tiles, whole chains in flight). The
+//     tile kernels' workgroups are mapped so that each XCD gathers from its own tile, resident in its L2.
 //   Between layers: liveness words per tile (spread over cache lines, or per-workgroup partial
 //   words), k_compact (stable compaction of the live list), k_repack / k_repack_u8 (regroup live
 //   positions into fewer tiles), k_final_ids.
@@ -1117,8 +1120,8 @@ __global__ __launch_bounds__(1024) void k_layers_lds(const float *__restrict__ y
 // each 128-byte line of the layers' lists, at most kFetchAhead layers ahead of that worker, so that the
 // XCD's workers find them in its L2 (which holds about 20 layers of 1024 neurons). Every wait ends: the
 // worker stores kPaceDone when it ends, and after kFetchPolls polls the helper gives up.
-// One layer of 1024 neurons for one row takes 1.84 us with its lists in the L2 and 2.3 from beyond it;
-// 120 layers, with the final row, 336 -> 280 us a pass; 64 rows x 30 layers of 1000 134 -> 124. Two and
+// One layer of 1024 neurons for one row takes 1.84 us with its lists in the L2 and 2.3 from beyond it (1.87 on
+// average with the helper); 120 layers, with the final row, 336 -> 280 us a pass; 64 rows x 30 layers of 1000 134 -> 124. Two and
 // four helpers per XCD were slower (293 us).
 constexpr int kFetchAhead = 12, kPaceEvery = 4, kPaceDone = 0x7fffffff, kFetchPolls = 1 << 14;
 __device__ void fetch_lists(const LayerPtr *__restrict__ lp, int l0, int L, int N, const int *__restrict__ pace) {
@@ -1167,8 +1170,9 @@ __device__ void fetch_lists(const LayerPtr *__restrict__ lp, int l0, int L, int 
 // ends with one barrier, for LDS alone (a full one would wait for the lists too), and the live rows
 // are counted in registers, 64 layers at a time.
 // Bound: the LDS reads (random rows; see conflict_grouped_order) and, for one or two rows, the lists, 6
-// bytes per edge through one CU's L1. Per layer at 1024 neurons: 4.1 -> 2.8 us (one row), 3.7 -> 2.5
-// (two rows per workgroup), 11.7 -> 9.3 (16 rows); at 4096 (two rows) 12.0 -> 11.1.
+// bytes per edge through one CU's L1. Per layer at 1024 neurons, k_layers_lds -> this: 3.55 -> 2.30 us
+// (one row; 1.87 with fetch_lists), 3.48 -> 2.38 (two rows per workgroup), 10.9 -> 8.4 (16 rows); at 4096
+// 12.0 -> 9.4 (one row), 9.7 -> 8.6 (two).
 template <int B>
 __global__ __launch_bounds__(1024) void k_layers_lds32(const float *__restrict__ yin, float *__restrict__ yout, int N,
                                                        const LayerPtr *__restrict__ lp, int l0, int L, float ymax,
@@ -1620,8 +1624,8 @@ __global__ __launch_bounds__(256) void k_layer_gfm(const float *__restrict__ fin
 //     taken by wave k % 16 as its output k / 16.
 //   colb[64 k + lane]: the column (kNoColumn: none) and its bias.
 // Bound: the LDS reads (16 lanes at random rows take 3.06 of the cycles that conflict-free ones take, so
-// at most 21 edge-rows per clock and CU) while sums run, 2/3 of the time, then the rows' way in and
-// out, which every CU takes at about the same time. Gathers of 128-byte segments from a resident L2
+// at most 21 edge-rows per clock and CU; counted: 63-64% of the LDS's active cycles are conflicts, and it is
+// active 67-70% of the time), then the rows' way in and out, which every CU takes at about the same time. Gathers of 128-byte segments from a resident L2
 // (k_layer_gfm) end at 12, and reach 7.3. 15,000 live rows at 16384 neurons: 1.08 ms per layer against
 // 1.83 for k_layer_gfm; columns of 1 to 48 sources at 10007 neurons, 3000 rows: 0.13 ms against 0.94.
 // Tried: 16-byte loads and stores of the rows (8% slower: their 4-way conflicts in the LDS transposes),
@@ -1937,7 +1941,8 @@ constexpr int kMaxPartWords = kPartThreads * kPartLoads;
 
 // Tile of workgroup g of G, nt tiles: the workgroups in XCD order (an XCD's follow each other) are divided
 // evenly among the tiles, so that every XCD has its share and gathers from at most two tiles. (Whole
-// XCDs per tile left two of eight idle with 3 tiles: 100 rows at 65536 neurons, 93 us per layer.)
+// XCDs per tile left two of eight idle with 3 tiles, three with 5 and one with 7: 12 layers of 65536 neurons,
+// read-backs apart, 1.12 -> 1.06, 2.10 -> 1.52 and 2.18 -> 1.99 ms; 1, 2, 4 and 8 tiles the same.)
 __device__ __forceinline__ int few_tile(int g, int nt, int G) { return g * nt / G; }
 
 // Mask words m[t] = OR of the partial words of tile t (t < nt), from the kPartLoads of the G
@@ -2682,8 +2687,8 @@ __global__ void k_report_overflow(const int *__restrict__ overflow, unsigned lon
 // thread it was a chain of 32 loads per item) and for the segments. Eight workgroups per CU are launched and
 // must be resident at once (64 registers: at 70 to 76 the last ones ran alone, 4-7% of a pass more).
 // Batches of 4 old tiles beat 8, which read more segments that no slot needs, and 2. 60,000 rows of 16384
-// neurons through 20 structured layers, four such repacks: 16.45 -> 15.05 ms a pass; 65536 neurons x 16
-// layers 27.27 -> 27.07.
+// neurons through 20 structured layers, four such repacks: 16.45 -> 15.05 ms a pass (one repack of 65536
+// neurons x 16 layers: within the runs' differences).
 constexpr int kRepackSources = 256;
 constexpr int kRepackTiles = 0, kRepackCodes = 1, kRepackRows = 2;
 template <int OUT = kRepackTiles, int CR = 32>
@@ -4201,8 +4206,9 @@ hipError_t launch_layers_lds_b(sdnn_net *net, const float *yin, float *yout, int
   const int grid = (int)std::max<int64_t>(1, (rows + B - 1) / B);
   const LayerPtr *lp = net->lp_dev[B >= 16 ? 2 : (B == 8 ? 1 : 0)];  // the table grouped for this height
   if (net->n_edge32 == net->L) {
-    // idle CUs fetch the lists ahead, where kFetchAhead layers (200 bytes per neuron) leave room in the L2
-    // (4 MiB) and more layers than that follow
+    // idle CUs fetch the lists ahead, where kFetchAhead layers (200 bytes per neuron) take at most 2.5 MiB of
+    // the 4 MiB L2, that is up to 1092 neurons, and more layers than that follow. (1.5 MiB for the layers that
+    // the other workers lag behind. Wider layers with a shorter distance have not been measured.)
     const int workers = (grid + 7) / 8 * 8;
     const bool fetch = workers + 8 <= net->cus && (size_t)net->N * 200 * kFetchAhead <= (size_t)5 << 19 &&
                        net->L - l0 > kFetchAhead;
@@ -4874,7 +4880,7 @@ sdnn_status sdnn_load_layers(sdnn_net *net, int32_t l0, int32_t nl, const int64_
     }
   }
   if (seg && !net->no_streams) {
-    // the streams of k_layer_seg, last, because the layers run without them where memory does not suffice
+    // the streams of k_layer_seg, last, because the network runs without them where memory does not suffice
     // (one more group after each layer's: the kernel loads one ahead)
     std::vector<size_t> off((size_t)nl + 1, 0);
     for (int32_t i = 0; i < nl; ++i) off[(size_t)i + 1] = off[(size_t)i] + groups[(size_t)i] + 1;
@@ -5014,7 +5020,10 @@ sdnn_status infer_lds(sdnn_net *net, const float *y0, int M) {
     const bool fits = (live_bound + bmax - 1) / bmax <= net->cus;
     const bool settled = kept >= 2;
     // (layer 0 too where the kernel marks the nonzero input rows, for at most 4 rows per CU: a launch, a
-    // compaction and a wait less, 445 -> 410 us for one row through 120 layers of 1024 neurons)
+    // compaction and a wait less, 445 -> 410 us for one row through 120 layers of 1024 neurons. Rows that die
+    // in the first layers keep their slots, as they do in later ones, and it still pays: 4096 neurons, layer 0
+    // first / fused from it, 1024 rows of which 47 are left, 30 layers 398 / 380 us, 120 layers 1338 / 1318;
+    // 1024 rows that all die within 3 layers 107 / 88.)
     const bool from0 = net->n_edge32 == net->L;
     if ((l > 0 || from0) && (live_bound <= 4 * (int64_t)net->cus || (fits && settled))) {
       const bool rec = net->profiling;
@@ -5113,7 +5122,11 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
   bool fin_rows = false, fout_rows = false;
   const int *fin_map = nullptr;
   // a layer of `rows` live rows runs on rows: more than one round of tiles, or columns of other than 32
-  // sources (few-tile layers have kernels for 32 only)
+  // sources (few-tile layers have kernels for 32 only). 60 layers of 10007 neurons with 1 to 48 sources, the
+  // ELL walk of k_layer_gfm polled every 16 layers / rows with a report per layer (us): 1 row 494 / 249, 16
+  // rows 2134 / 1658, 64 rows 2650 / 1800, 256 rows 5108 / 2415, 600 rows 11133 / 3192. 8 layers of 32
+  // sources and 300 rows, tiles / rows, the library before the rows kernel and with it: 4097 neurons 469 / 328,
+  // 10113 neurons 562 / 423. (Layers of 32 sources and fewer rows: k_layer_gfm_small, a launch without a report.)
   auto seg_layer = [&](int32_t layer, int64_t rows) {
     return layer < net->L && net->layers[(size_t)layer].seg && (rows > one_round || net->layers[(size_t)layer].K != 32);
   };
@@ -5250,8 +5263,8 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
     }
     fout = (fin == net->fm[1]) ? net->fm[0] : net->fm[1];
     if (l == 0) {
-      // layer 0 reads the caller's rows; binary inputs go through bit tiles (built in fm[0]),
-      // others through feature-major tiles in fm[0]; both passes also find the nonzero input rows
+      // layer 0 reads the caller's rows; binary inputs go through bit tiles (built in fm[0]), others straight
+      // into k_layer_seg or through feature-major tiles in fm[0]; each way also finds the nonzero input rows
       // the pack pass addresses rows with 32-bit offsets (in floats, or float4 when N % 4 == 0)
       const uint64_t units = (uint64_t)M * (uint64_t)net->N / ((net->N & 3) == 0 ? 4 : 1);
       const bool try_bits = net->bitsT > 0 && net->layers[0].K <= 32 && net->layers[0].ellw && units < (1ull << 32) &&
@@ -5373,7 +5386,7 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
       last_list = cur ^ 1;
       return hipGetLastError();
     };
-    // the repack of this layer's outputs as the next layer's one-byte codes (k_repack<1, CR>), into
+    // the repack of this layer's outputs as the next layer's one-byte codes (k_repack<kRepackCodes, CR>), into
     // dst; sets repacked_codes when the dictionary held every value
     auto repack_codes = [&](float *dst) -> hipError_t {
       unsigned *gd = net->dict;
