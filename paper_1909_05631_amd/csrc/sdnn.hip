@@ -5174,7 +5174,9 @@ sdnn_status infer_gfm(sdnn_net *net, const float *y0, int M) {
   int32_t l = 0;
   for (; l < net->L && live_bound > 0; ++l) {
     const bool few = l > 0 && P <= one_round;
-    const bool small = few && !fin_rows;
+    // (a layer on rows or codes, however few, leaves its liveness in the spread words, which only the compaction
+    // right after it reads)
+    const bool small = few && !fin_rows && !fin_codes;
     bool reported = false;  // this layer's launch writes the progress word
     fout_codes = false;
     fout_rows = false;

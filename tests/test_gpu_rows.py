@@ -134,6 +134,30 @@ def test_rows_to_codes_and_back():
     assert cats.size == m
 
 
+@pytest.mark.parametrize("equal", [False, True])
+@pytest.mark.parametrize("n,m,nl", [(6000, 300, 2), (6000, 300, 3), (6000, 300, 6), (6000, 700, 5), (40000, 300, 5)])
+def test_codes_to_few_rows(n, m, nl, equal):
+    """Binary inputs whose live rows fall to at most 256 in layer 0, which wrote codes: the layer that reads the
+    codes of few rows counts its live rows, and those after it go on from its outputs."""
+    rng = np.random.default_rng(n + m)
+    dens = np.where(rng.random((m, 1)) < 200 / m, 0.6, 0.002)
+    y0 = (rng.random((m, n)) < dens).astype(np.float32)
+    layers = []
+    for l in range(nl):
+        cp, src, v, b = offset_layer(rng, n, -0.3)
+        layers.append((cp, src, np.full_like(v, 1.0 / 16.0), b))
+    log(f"codes to few rows n={n} m={m} layers={nl} equal={equal}")
+    gpu = GpuNet(n, nl, equal_values=equal)
+    for l, layer_ in enumerate(layers):
+        gpu.load(l, *layer_)
+    cats = gpu.run(y0)
+    o = oracle_run(y0, layers)
+    assert 0 < oracle.padded_live_counts(o, nl)[1] <= 256
+    kinds = gpu.net.layer_info()[0]
+    assert kinds[0] in (6, 7) and kinds[1] == 3  # codes written and read
+    assert_parity(gpu, o, cats)
+
+
 def test_two_handles_in_turn():
     """Two networks of one width on one stream keep their own rows and maps."""
     n, m = 9000, 600
