@@ -1625,7 +1625,8 @@ __global__ __launch_bounds__(256) void k_layer_gfm(const float *__restrict__ fin
 //   colb[64 k + lane]: the column (kNoColumn: none) and its bias.
 // Bound: the LDS reads (16 lanes at random rows take 3.06 of the cycles that conflict-free ones take, so
 // at most 21 edge-rows per clock and CU; counted: 63-64% of the LDS's active cycles are conflicts, and it is
-// active 67-70% of the time), then the rows' way in and out, which every CU takes at about the same time. Gathers of 128-byte segments from a resident L2
+// active 68-71% of the time), then the rows' way in and out, which every CU takes at about the same time.
+// Gathers of 128-byte segments from a resident L2
 // (k_layer_gfm) end at 12, and reach 7.3. 15,000 live rows at 16384 neurons: 1.08 ms per layer against
 // 1.83 for k_layer_gfm; columns of 1 to 48 sources at 10007 neurons, 3000 rows: 0.13 ms against 0.94.
 // Tried: 16-byte loads and stores of the rows (8% slower: their 4-way conflicts in the LDS transposes),
