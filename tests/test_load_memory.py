@@ -12,7 +12,7 @@ from paper_1909_05631_amd import sdnn
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
-DRIVER = r"""
+PROGRAM = r"""
 #include <atomic>
 #include <cstdio>
 #include <cstdlib>
@@ -102,7 +102,7 @@ int main(int argc, char **argv) {
 
 
 @pytest.fixture(scope="module")
-def driver(tmp_path_factory):
+def program(tmp_path_factory):
     gxx = shutil.which("g++")
     if gxx is None:
         pytest.skip("needs g++")
@@ -110,14 +110,14 @@ def driver(tmp_path_factory):
         from paper_1909_05631_amd import build
         build.build()
     d = tmp_path_factory.mktemp("load_memory")
-    src, exe = d / "driver.cc", d / "driver"
-    src.write_text(DRIVER)
+    src, exe = d / "program.cc", d / "program"
+    src.write_text(PROGRAM)
     subprocess.run([gxx, "-O1", "-std=c++17", "-rdynamic", "-I", os.path.join(ROOT, "include"), "-o", str(exe), str(src),
                     "-ldl"], check=True)
     return str(exe)
 
 
 @pytest.mark.parametrize("n,equal", [(256, 0), (4224, 0), (4224, 1)])
-def test_out_of_host_memory(driver, n, equal):
-    r = subprocess.run([driver, sdnn.library_path(), str(n), str(equal)], capture_output=True, text=True, timeout=600)
+def test_out_of_host_memory(program, n, equal):
+    r = subprocess.run([program, sdnn.library_path(), str(n), str(equal)], capture_output=True, text=True, timeout=600)
     assert r.returncode == 0, f"exit status {r.returncode}: {r.stdout[-500:]}{r.stderr[-500:]}"
